@@ -4,45 +4,18 @@
 // full-vocabulary online log-sum-exp epilogue that never writes logits.
 //
 // Large problems use 256x256 tiles (8 waves, MFMA fragments read one step
-// ahead; in the pair mode the hi and lo planes of A share each B tile);
-// problems with too few such tiles to fill the 256 CUs use 256x128 tiles
-// (8 waves of 64x64, three stages). Both feed
-// LDS with direct global->LDS loads, one barrier per K step. Tiles are ordered
-// so that each XCD works on a contiguous band (see tile_coords).
+// ahead; in the pair mode the hi and lo planes of A share each B tile) fed by
+// direct global->LDS loads, one barrier per K step. Problems of few tiles
+// take the smaller tiles of gemm_small.h; which one is chosen by the estimated
+// time of its rounds of workgroups (small_tile_for). Tiles are ordered so that
+// each XCD works on a contiguous band (see tile_coords).
 #include <algorithm>
 
 #include "gemm_core.h"
+#include "gemm_small_tiles.h"
 #include "kernels.h"
 
 namespace jetk {
-
-template <typename T>
-struct GemmArgs {
-  const T *A;
-  const T *B;
-  int64_t lda, ldb;
-  int M, N;
-  int K, KA, KB;  // K steps over K columns; A column k mod KA, B column k mod KB
-  void *out;
-  int64_t ldo;
-  int pair_out;   // SwiGLU / QKV-RoPE: write (hi, lo) pairs
-  float oscale;   // every product is multiplied by oscale before the epilogue
-  QkvRope rope;   // EPI_QKV_ROPE only
-  // grouped GEMM: row tile t uses B + tile_group[t] * group_stride; tiles
-  // with tile_group -1 do nothing (null: one B for all tiles)
-  const int *tile_group = nullptr;
-  int64_t group_stride = 0;
-  // int8 B (LOAD 9 configurations): fp16 scales [K / 32][ceil(N / 128)][32][4]
-  const uint16_t *Bs = nullptr;
-};
-
-// (hi, lo) split of v stored at p[0] and p[ps] (lo only with pair).
-template <typename T>
-__device__ __forceinline__ void put_split(T *p, int64_t ps, float v, int pair) {
-  const T hi = from_f<T>(v);
-  p[0] = hi;
-  if (pair) p[ps] = from_f<T>(v - to_f<T>(hi));
-}
 
 // Orders a wave's LDS writes before its following LDS reads of other lanes'
 // data (a wave's LDS operations complete in order).
@@ -161,15 +134,6 @@ template <class C, int EPI>
 __global__ __launch_bounds__(C::NT) void gemm_kernel(GemmArgs<typename C::type> g) {
   using T = typename C::type;
   extern __shared__ uint4 lds[];
-  if (gridDim.y > 1) {
-    // split K (plain operands, fp32 store): workgroup row y takes K columns
-    // [y Kc, (y + 1) Kc) and writes its partial sums to slice y of out
-    const int kc = g.K / (int)gridDim.y;
-    g.A += (int64_t)blockIdx.y * kc;
-    g.B += (int64_t)blockIdx.y * kc;
-    g.K = g.KA = g.KB = kc;
-    g.out = (float *)g.out + (int64_t)blockIdx.y * g.M * g.ldo;
-  }
   const int nt_m = (g.M + C::BM - 1) / C::BM, nt_n = (g.N + C::BN - 1) / C::BN;
   int tm, tn;
   tile_coords(nt_m, nt_n, &tm, &tn);
@@ -373,8 +337,8 @@ using BigB = GCfg<bf16, 256, 256, 128, 64, 4, 1, 2, 8>;
 // over the first MFMA step of the step before), waves of 64 x 128 so each B
 // fragment serves both planes.
 using PairB = GCfg<bf16, 256, 256, 64, 128, 7, 2, 3, 4>;
-// ... and for problems with fewer tiles: 128x128 tiles (8 waves of 32x64,
-// three 24 KB stages, two workgroups per CU).
+// ... and 128x128 tiles (8 waves of 32x64, three 24 KB stages, two workgroups
+// per CU) for problems of few tiles whose K is too short for gemm_small.h.
 using PairS = GCfg<bf16, 128, 128, 32, 64, 7, 2, 3, 4>;
 using SmallB = GCfg<bf16, 256, 128, 64, 64, 2, 1, 3, 8>;
 using CfgF = GCfg<float, 128, 128, 64, 64, 0, 1>;
@@ -382,7 +346,8 @@ using LmB = GCfg<bf16, 256, 256, 128, 64, 4, 1, 2, 8>;
 using LmF = GCfg<float, 128, 128, 64, 64, 0, 1>;
 // fp16 operands: the LOAD 7 schedule with a single A plane (three 32 KB
 // stages of 32-column A and B tiles), 256x256 tiles with waves of 64 x 128,
-// or 128x128 tiles for problems with fewer tiles; the LM head on the same
+// or 128x128 tiles (the last round of a large launch, grouped GEMMs, and
+// problems of few tiles whose K is too short for gemm_small.h); the LM head on the same
 // 256x256 schedule (16% faster than the two-stage 128-byte-row one).
 using HalfB = GCfg<f16, 256, 256, 64, 128, 8, 2, 3, 4>;
 using HalfS = GCfg<f16, 128, 128, 32, 64, 8, 2, 3, 4>;
@@ -403,13 +368,6 @@ using Q8S = GCfg<f16, 128, 128, 64, 64, 9, 2, 3, 4>;
 // int4 B (packed two per byte), the same schedule
 using Q4B = GCfg<f16, 256, 256, 64, 128, 10, 2, 3, 4>;
 using Q4S = GCfg<f16, 128, 128, 64, 64, 10, 2, 3, 4>;
-
-// Kernels whose LDS exceeds the default 64 KB limit must opt in once.
-template <class C>
-static hipError_t allow_lds(const void *fn) {
-  if (C::LDS_BYTES <= 65536) return hipSuccess;
-  return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS_BYTES);
-}
 
 template <class C, int EPI>
 static hipError_t run_gemm(const void *A, int64_t lda, const void *B, int64_t ldb, int M, int N, int K, int pair,
@@ -436,43 +394,6 @@ static hipError_t run_epi(int epi, const void *A, int64_t lda, const void *B, in
 }
 
 int gemm_k_step(int dtype) { return dtype == 1 ? CfgF::BK : BigB::BK; }
-
-// Fixed-order sum of the split-K partials: out (+)= sum over s of part[s].
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restrict__ part, int S, int M, int N,
-                                                            float *__restrict__ out, int64_t ldo, int add) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (int64_t)M * N) return;
-  const int r = (int)(i / N), c = (int)(i % N);
-  float v = 0.0f;
-  for (int s = 0; s < S; ++s) v += part[((int64_t)s * M + r) * N + c];
-  float *o = out + (int64_t)r * ldo + c;
-  *o = add ? *o + v : v;
-}
-
-int gemm_splitk_ways(int dtype, int pair, int M, int N, int K) {
-  if (dtype != 2 || pair) return 1;
-  const int tiles = ((M + HalfS::BM - 1) / HalfS::BM) * ((N + HalfS::BN - 1) / HalfS::BN);
-  int s = 1;
-  while (s < 16 && tiles * s < 256 && K % (2 * s * HalfS::BK) == 0 && K / (2 * s) >= 512) s *= 2;
-  return s;
-}
-
-hipError_t launch_gemm_splitk(int epi, const void *A, int64_t lda, const void *B, int64_t ldb, int M, int N, int K,
-                              int S, float *part, void *out, int64_t ldo, float oscale, hipStream_t st) {
-  if (M <= 0 || N <= 0) return hipSuccess;
-  if (S < 2 || K % (S * HalfS::BK) || (epi != EPI_STORE_F32 && epi != EPI_RESID_ADD)) return hipErrorInvalidValue;
-  static const hipError_t once = allow_lds<HalfS>((const void *)gemm_kernel<HalfS, 0>);
-  if (once != hipSuccess) return once;
-  GemmArgs<f16> g{(const f16 *)A, (const f16 *)B, lda, ldb, M, N, K, K, K, part, N, 0, oscale, QkvRope{}};
-  const int tiles = ((M + HalfS::BM - 1) / HalfS::BM) * ((N + HalfS::BN - 1) / HalfS::BN);
-  hipLaunchKernelGGL((gemm_kernel<HalfS, 0>), dim3(tiles, S), dim3(HalfS::NT), HalfS::LDS_BYTES, st, g);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int64_t n = (int64_t)M * N;
-  hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, part, S, M, N,
-                     (float *)out, ldo, epi == EPI_RESID_ADD ? 1 : 0);
-  return hipGetLastError();
-}
 
 // Workgroups of gemm_kernel<C, EPI> the device holds at once (0 if unknown).
 template <class C, int EPI>
@@ -510,23 +431,81 @@ static hipError_t run_gemm_tail(const void *A, int64_t lda, const void *B, int64
                               (char *)out + (size_t)M1 * (size_t)ldo * osz, ldo, oscale, st);
 }
 
+// Estimated time of a launch: rounds of workgroups, one per CU.
+static double tile_us(const TileCost &c, int M, int N, int K) {
+  if (K % c.bk || K / c.bk < c.ahead) return 1e30;
+  const int64_t tiles = (int64_t)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+  return (double)((tiles + 255) / 256) * (c.a + c.b * K / 1000.0);
+}
+
+template <int N>
+static int cheapest(const TileCost (&c)[N], int M, int Nn, int K, double *us) {
+  int best = -1;
+  for (int i = 0; i < N; ++i) {
+    const double t = tile_us(c[i], M, Nn, K);
+    if (t < *us) *us = t, best = i;
+  }
+  return best;
+}
+
+template <typename T, int NPL, int QB>
+static int cheapest_of(int epi, int M, int N, int K, double *us) {
+  if (epi == EPI_SWIGLU) return cheapest(SmallSwiglu<T, NPL, QB>::cost, M, N, K, us);
+  if (epi == EPI_QKV_ROPE) return cheapest(SmallRope<T, NPL, QB>::cost, M, N, K, us);
+  return cheapest(SmallPlain<T, NPL, QB>::cost, M, N, K, us);
+}
+
+// The small tile to use for a problem, or -1 where the 256x256 tiles (big_us:
+// their cost per round, in the same model) are the cheaper ones. Those keep
+// every launch of 1024 or more such tiles: over so many rounds the last one
+// does not matter, and per element they are the fastest.
+template <typename T, int NPL, int QB>
+static int small_tile_for(int epi, int M, int N, int K, const TileCost &big) {
+  const int64_t big_tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
+  if (big_tiles >= 1024) return -1;
+  double us = tile_us(big, M, N, K);
+  return cheapest_of<T, NPL, QB>(epi, M, N, K, &us);
+}
+
+// Costs of the 256x256 tiles: fp16, (hi, lo) pairs, block-quantized B.
+static constexpr TileCost kBigF16{256, 256, 32, 1, 14.0, 23.0}, kBigPair{256, 256, 32, 1, 12.0, 43.0},
+    kBigQ{256, 256, 32, 1, 14.0, 27.0};
+
+// Arguments of one GEMM launch.
+template <typename T>
+static GemmArgs<T> gemm_args(const void *A, int64_t lda, const void *B, int64_t ldb, int M, int N, int K, int pair,
+                             void *out, int64_t ldo, float oscale, const uint16_t *Bs = nullptr) {
+  GemmArgs<T> g{(const T *)A, (const T *)B, lda, ldb, M, N, pair ? 2 * K : K, pair ? 2 * K : K, K, out, ldo, pair,
+                oscale, QkvRope{}};
+  g.Bs = Bs;
+  return g;
+}
+
 hipError_t launch_gemm(int dtype, int epi, const void *A, int64_t lda, const void *B, int64_t ldb, int M, int N,
                        int K, int pair, void *out, int64_t ldo, float oscale, hipStream_t st) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  // 256x256 tiles when there are enough of them to fill the chip twice over
   const int64_t big_tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
   if (dtype == 0) {
-    if (pair)
-      return big_tiles >= 512 ? run_epi<PairB>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st)
+    if (pair) {
+      const int c = epi == EPI_STORE_T ? -1 : small_tile_for<bf16, 2, 0>(epi, M, N, K, kBigPair);
+      if (c >= 0) return small_gemm_bf16p(epi, c, gemm_args<bf16>(A, lda, B, ldb, M, N, K, 1, out, ldo, oscale), st);
+      // (few tiles only where K is too short for the small tiles' ring)
+      return big_tiles >= 128 ? run_epi<PairB>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st)
                               : run_epi<PairS>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st);
+    }
     if (big_tiles >= 512) return run_epi<BigB>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st);
     return run_epi<SmallB>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st);
   }
   if (dtype == 2) {
-    if (pair)
-      return big_tiles >= 512 ? run_epi<HalfPairB>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st)
+    if (pair) {
+      const int c = epi == EPI_STORE_T ? -1 : small_tile_for<f16, 2, 0>(epi, M, N, K, kBigPair);
+      if (c >= 0) return small_gemm_f16p(epi, c, gemm_args<f16>(A, lda, B, ldb, M, N, K, 1, out, ldo, oscale), st);
+      return big_tiles >= 128 ? run_epi<HalfPairB>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st)
                               : run_epi<HalfPairS>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st);
-    if (big_tiles < 512) return run_epi<HalfS>(epi, A, lda, B, ldb, M, N, K, 0, out, ldo, oscale, st);
+    }
+    const int c = small_tile_for<f16, 1, 0>(epi, M, N, K, kBigF16);
+    if (c >= 0) return small_gemm_f16(epi, c, gemm_args<f16>(A, lda, B, ldb, M, N, K, 0, out, ldo, oscale), st);
+    if (big_tiles < 128) return run_epi<HalfS>(epi, A, lda, B, ldb, M, N, K, 0, out, ldo, oscale, st);
     if (epi == EPI_RESID_ADD && K <= 2048)
       return run_gemm_tail<HalfM, 1>(A, lda, B, ldb, M, N, K, out, ldo, oscale, st);
     switch (epi) {
@@ -567,8 +546,11 @@ hipError_t launch_gemm_q8(int epi, const void *A, int64_t lda, const void *Bq, c
                           int K, void *out, int64_t ldo, float oscale, hipStream_t st) {
   if (M <= 0 || N <= 0) return hipSuccess;
   if (K % 32 != 0) return hipErrorInvalidValue;
+  const int c = epi == EPI_STORE_T ? -1 : small_tile_for<f16, 1, 8>(epi, M, N, K, kBigQ);
+  if (c >= 0)
+    return small_gemm_q8(epi, c, gemm_args<f16>(A, lda, Bq, (int64_t)K * 8 / 8, M, N, K, 0, out, ldo, oscale, Bs), st);
   const int64_t big_tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
-  if (big_tiles >= 512) return run_q8_epi<Q8B>(epi, A, lda, Bq, Bs, M, N, K, out, ldo, oscale, st);
+  if (big_tiles >= 128) return run_q8_epi<Q8B>(epi, A, lda, Bq, Bs, M, N, K, out, ldo, oscale, st);
   return run_q8_epi<Q8S>(epi, A, lda, Bq, Bs, M, N, K, out, ldo, oscale, st);
 }
 
@@ -576,8 +558,11 @@ hipError_t launch_gemm_q4(int epi, const void *A, int64_t lda, const void *Bq, c
                           int K, void *out, int64_t ldo, float oscale, hipStream_t st) {
   if (M <= 0 || N <= 0) return hipSuccess;
   if (K % 32 != 0) return hipErrorInvalidValue;
+  const int c = epi == EPI_STORE_T ? -1 : small_tile_for<f16, 1, 4>(epi, M, N, K, kBigQ);
+  if (c >= 0)
+    return small_gemm_q4(epi, c, gemm_args<f16>(A, lda, Bq, (int64_t)K * 4 / 8, M, N, K, 0, out, ldo, oscale, Bs), st);
   const int64_t big_tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
-  if (big_tiles >= 512) return run_q8_epi<Q4B>(epi, A, lda, Bq, Bs, M, N, K, out, ldo, oscale, st);
+  if (big_tiles >= 128) return run_q8_epi<Q4B>(epi, A, lda, Bq, Bs, M, N, K, out, ldo, oscale, st);
   return run_q8_epi<Q4S>(epi, A, lda, Bq, Bs, M, N, K, out, ldo, oscale, st);
 }
 
@@ -643,16 +628,43 @@ static hipError_t run_qkv_rope(const void *A, int64_t lda, const void *B, int64_
   return hipGetLastError();
 }
 
-bool gemm_qkv_rope_ok(int dtype, int pair, int M, int N, int head_dim) {
-  if (head_dim != 128 || N % 128 || M <= 0) return false;
-  const int64_t big_tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
-  // the 256x256 configurations have waves of 128 columns
-  return (dtype == 0 && pair && big_tiles >= 512) || (dtype == 2 && big_tiles >= 512);
+// Small RoPE tile for a problem (-1: none), and whether the 256x256 tiles,
+// whose waves of 128 columns hold a head each, can run it.
+static int rope_tile_for(int dtype, int qbits, int pair, int M, int N, int K) {
+  if (qbits == 8) return small_tile_for<f16, 1, 8>(EPI_QKV_ROPE, M, N, K, TileCost{256, 256, 32, 1, 1e30, 0});
+  if (qbits == 4) return small_tile_for<f16, 1, 4>(EPI_QKV_ROPE, M, N, K, TileCost{256, 256, 32, 1, 1e30, 0});
+  if (dtype == 0) return pair ? small_tile_for<bf16, 2, 0>(EPI_QKV_ROPE, M, N, K, kBigPair) : -1;
+  if (pair) return small_tile_for<f16, 2, 0>(EPI_QKV_ROPE, M, N, K, kBigPair);
+  return small_tile_for<f16, 1, 0>(EPI_QKV_ROPE, M, N, K, kBigF16);
+}
+static bool rope_big_ok(int dtype, int qbits, int pair, int M, int N) {
+  return !qbits && (dtype == 2 || (dtype == 0 && pair)) &&
+         (int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 128;
 }
 
-hipError_t launch_gemm_qkv_rope(int dtype, const void *A, int64_t lda, const void *B, int64_t ldb, int M, int N,
-                                int K, int pair, float oscale, const QkvRope &r, hipStream_t st) {
-  if (!gemm_qkv_rope_ok(dtype, pair, M, N, 128)) return hipErrorInvalidValue;
+bool gemm_qkv_rope_ok(int dtype, int qbits, int pair, int M, int N, int K, int head_dim) {
+  if (head_dim != 128 || N % 128 || M <= 0 || dtype == 1) return false;
+  return rope_tile_for(dtype, qbits, pair, M, N, K) >= 0 || rope_big_ok(dtype, qbits, pair, M, N);
+}
+
+hipError_t launch_gemm_qkv_rope(int dtype, int qbits, const void *A, int64_t lda, const void *B, const uint16_t *Bs,
+                                int64_t ldb, int M, int N, int K, int pair, float oscale, const QkvRope &r,
+                                hipStream_t st) {
+  if (!gemm_qkv_rope_ok(dtype, qbits, pair, M, N, K, 128)) return hipErrorInvalidValue;
+  const int c = rope_tile_for(dtype, qbits, pair, M, N, K);
+  if (c >= 0) {
+    if (dtype == 0) {
+      GemmArgs<bf16> g = gemm_args<bf16>(A, lda, B, ldb, M, N, K, pair, nullptr, 0, oscale);
+      g.rope = r;
+      return small_gemm_bf16p(EPI_QKV_ROPE, c, g, st);
+    }
+    GemmArgs<f16> g = gemm_args<f16>(A, lda, B, qbits ? (int64_t)K * qbits / 8 : ldb, M, N, K, pair, nullptr, 0,
+                                     oscale, Bs);
+    g.rope = r;
+    if (qbits == 8) return small_gemm_q8(EPI_QKV_ROPE, c, g, st);
+    if (qbits == 4) return small_gemm_q4(EPI_QKV_ROPE, c, g, st);
+    return pair ? small_gemm_f16p(EPI_QKV_ROPE, c, g, st) : small_gemm_f16(EPI_QKV_ROPE, c, g, st);
+  }
   if (dtype == 0) return run_qkv_rope<PairB>(A, lda, B, ldb, M, N, K, pair, oscale, r, st);
   if (pair) return run_qkv_rope<HalfPairB>(A, lda, B, ldb, M, N, K, pair, oscale, r, st);
   return run_qkv_rope<HalfB>(A, lda, B, ldb, M, N, K, 0, oscale, r, st);

@@ -1,0 +1,10 @@
+// Small-tile GEMMs (gemm_small.h): fp16 operands, int4 block-quantized B.
+#include "gemm_small_tiles.h"
+
+namespace jetk {
+
+hipError_t small_gemm_q4(int epi, int cfg, const GemmArgs<f16> &g, hipStream_t st) {
+  return run_small_tiles<f16, 1, 4>(epi, cfg, g, st);
+}
+
+}  // namespace jetk

@@ -25,18 +25,13 @@ struct QkvRope {
   void *k_cache, *v_cache;  // [planes][Hkv][S][128]
   int64_t kv_ps, S, slot0;
 };
-// Split-K for GEMMs of few rows (fp16, plain operands): the number of K
-// chunks worth running (1 = none), and the launch: S chunks of K / S columns
-// each write fp32 partial sums to part [S][M][N], then a fixed-order sum
-// stores them (EPI_STORE_F32) or adds them (EPI_RESID_ADD) to out.
-int gemm_splitk_ways(int dtype, int pair, int M, int N, int K);
-hipError_t launch_gemm_splitk(int epi, const void *A, int64_t lda, const void *B, int64_t ldb, int M, int N, int K,
-                              int S, float *part, void *out, int64_t ldo, float oscale, hipStream_t st);
 // Whether launch_gemm_qkv_rope can run this problem (head_dim 128 and a tile
-// configuration whose waves cover whole heads).
-bool gemm_qkv_rope_ok(int dtype, int pair, int M, int N, int head_dim);
-hipError_t launch_gemm_qkv_rope(int dtype, const void *A, int64_t lda, const void *B, int64_t ldb, int M, int N,
-                                int K, int pair, float oscale, const QkvRope &r, hipStream_t st);
+// configuration whose waves hold both dims of a rotation pair). qbits: 0, or
+// the bits of a block-quantized B (with Bs and B as in launch_gemm_q8 / _q4).
+bool gemm_qkv_rope_ok(int dtype, int qbits, int pair, int M, int N, int K, int head_dim);
+hipError_t launch_gemm_qkv_rope(int dtype, int qbits, const void *A, int64_t lda, const void *B, const uint16_t *Bs,
+                                int64_t ldb, int M, int N, int K, int pair, float oscale, const QkvRope &r,
+                                hipStream_t st);
 
 // C[M x N] (epilogue) A[M x K] * B[N x K]^T. K must be a multiple of
 // gemm_k_step(dtype). pair (bf16 only): every A row holds a (hi, lo) bf16

@@ -631,18 +631,6 @@ Status run_gemm(jet_model *m, int cls, int epi, const void *A, int64_t lda, int 
     else LAUNCH(jetk::launch_gemm_q8(epi, A, lda, B, Bs, (int)M, (int)N, (int)K, out, ldo, oscale, m->st));
     return Status::ok();
   }
-  // decode steps (one row per question): too few output tiles to fill the
-  // device, so K is split across workgroups and summed in a fixed order
-  if (m->splitk && (epi == jetk::EPI_STORE_F32 || epi == jetk::EPI_RESID_ADD)) {
-    const int S = jetk::gemm_splitk_ways(m->kdt, pair, (int)M, (int)N, (int)K);
-    if (S > 1) {
-      float *part;
-      TRY(ws_t<float>(m, "splitk_part", (size_t)(S * M * N), &part));
-      LAUNCH(jetk::launch_gemm_splitk(epi, A, lda, B, ldb, (int)M, (int)N, (int)K, S, part, out, ldo, oscale,
-                                      m->st));
-      return Status::ok();
-    }
-  }
   LAUNCH(jetk::launch_gemm(m->kdt, epi, A, lda, B, ldb, (int)M, (int)N, (int)K, pair, out, ldo, oscale, m->st));
   return Status::ok();
 }
@@ -945,15 +933,16 @@ Status attn_in(jet_model *m, const Layer &ly, const WaveBufs &b, int64_t R, cons
     LAUNCH(jetk::launch_rmsnorm(m->kdt, m->apair, b.resid, nullptr, ly.attn_norm, (int)R, (int)h.d,
                                 (float)h.rms_eps, b.xn, m->st));
   }
-  if (!ly.s_qkv && jetk::gemm_qkv_rope_ok(m->kdt, m->apair, (int)R, (int)nqkv, (int)h.head_dim)) {
+  const int qbits = ly.s_qkv ? h.qbits : 0;
+  if (jetk::gemm_qkv_rope_ok(m->kdt, qbits, m->apair, (int)R, (int)nqkv, (int)h.d, (int)h.head_dim)) {
     // projection, RoPE and the K/V scatter in one kernel
     const double out_bytes = (double)R * (double)nqkv * (double)m->esz * m->anp;
     KTimer t(m, JET_K_GEMM_QKV, gemm_flops(R, nqkv, h.d),
              (double)(R * h.d * m->anp + nqkv * h.d) * (double)m->esz + out_bytes);
     jetk::QkvRope r{d_pos, m->rope_cos, m->rope_sin, (int)h.n_heads, (int)h.n_kv_heads, b.q,
                     R * h.n_heads * h.head_dim, kc, vc, h.n_kv_heads * S * h.head_dim, S, slot0};
-    LAUNCH(jetk::launch_gemm_qkv_rope(m->kdt, b.xn, m->anp * h.d, ly.w_qkv, h.d, (int)R, (int)nqkv, (int)h.d, m->apair,
-                                      ly.is_qkv, r, m->st));
+    LAUNCH(jetk::launch_gemm_qkv_rope(m->kdt, qbits, b.xn, m->anp * h.d, ly.w_qkv, ly.s_qkv, h.d, (int)R, (int)nqkv,
+                                      (int)h.d, m->apair, ly.is_qkv, r, m->st));
     return Status::ok();
   }
   TRY(run_gemm(m, JET_K_GEMM_QKV, jetk::EPI_STORE_F32, b.xn, m->anp * h.d, m->apair, ly.w_qkv, h.d, R, nqkv, h.d,
@@ -1302,11 +1291,6 @@ Status generate(jet_model *m, jet_prefix *p, int32_t n, float tau, uint64_t seed
     if (offs[q + 1] - offs[q] + n > m->max_ctx)
       return Status::err(JET_E_CAPACITY, "prefix " + std::to_string(q) + " plus the trace is longer than max_ctx");
   if (n == 0) return Status::ok();
-  struct SplitK {  // split-K GEMMs for the decode steps of this call only
-    jet_model *m;
-    explicit SplitK(jet_model *mm) : m(mm) { m->splitk = true; }
-    ~SplitK() { m->splitk = false; }
-  } splitk_scope(m);
   const bool out_dev = out && is_device_ptr(out);
   const int64_t T = p->T, T2 = T + (int64_t)nq * n, V = h.vocab;
   std::vector<int64_t> offs2((size_t)nq + 1);

@@ -1,0 +1,67 @@
+"""GEMM tile choice: a row's result does not depend on the tile its batch
+size selects.
+
+One question alone runs on the smallest tiles, the same question inside a
+batch on larger ones, and every tile adds the same products in the same order,
+so the scores agree bit for bit. Prefix lengths sit at and around tile edges;
+the widths give K loops of a few steps (one too short for some tiles' rings)
+and column remainders. The batch is checked against the fp64 oracle.
+"""
+import numpy as np
+import pytest
+
+import jet_synth
+import oracle
+from paper_2609_33874_amd import jet as J
+
+pytestmark = pytest.mark.gpu
+
+DENSE = dict(arch="dense", n_layers=2, n_heads=6, n_kv_heads=2, head_dim=128, vocab=1100, max_ctx=1024)
+CASES = {
+    "f16": (dict(DENSE, dtype="bf16", d_model=768, ffn=1088), J.JET_F16),
+    "f16_short_k": (dict(DENSE, dtype="bf16", d_model=320, ffn=448), J.JET_F16),
+    "bf16_pair": (dict(DENSE, dtype="bf16", d_model=768, ffn=1088), J.JET_BF16),
+    "f16_pair": (dict(DENSE, dtype="bf16", d_model=768, ffn=1088), J.JET_F16P),
+    "q8": (dict(DENSE, dtype="q8", d_model=768, ffn=1024), J.JET_F16),
+    "q4": (dict(DENSE, dtype="q4", d_model=768, ffn=1024), J.JET_F16),
+    "hybrid_pair": (dict(DENSE, arch="hybrid", n_layers=4, dtype="bf16", d_model=640, ffn=832, gdn_heads=5,
+                         gdn_dk=128, gdn_dv=128, conv_kernel=4), J.JET_BF16),
+}
+PREFIX = [1, 2, 15, 16, 17, 31, 33, 63, 64, 65, 127, 129, 200, 257, 300]
+
+
+@pytest.mark.parametrize("case", list(CASES))
+def test_scores_do_not_depend_on_the_tile(case, tmp_path):
+    spec, mode = CASES[case]
+    path = str(tmp_path / "m.jetm")
+    jet_synth.write_model(path, spec)
+    g = np.random.Generator(np.random.Philox(key=[3, len(case)]))
+    pre = [g.integers(0, spec["vocab"], n).astype(np.int32) for n in PREFIX]
+    cand = [[g.integers(0, spec["vocab"], m).astype(np.int32) for m in (1, 1 + q % 5, 9)] for q in range(len(pre))]
+    few = jet_synth.from_lists(pre, cand)
+    # the same questions again with 60 more, so that the batch has many tiles
+    more = [g.integers(0, spec["vocab"], 280).astype(np.int32) for _ in range(60)]
+    many = jet_synth.from_lists(pre + more, cand + [[y[:7] for y in more[q:q + 1]] for q in range(60)])
+    m = J.jet_model_load(path, dtype=mode)
+    try:
+        def score(w):
+            p = J.jet_prefill_prefix(m, w.prefix_offsets, w.prefix_tokens)
+            out = J.jet_score_candidates(m, p, w.q_cand_offsets, w.cand_tok_offsets, w.cand_tokens)
+            J.jet_prefix_free(p)
+            return out
+
+        tok, tot = score(few)
+        tok_many, tot_many = score(many)
+        np.testing.assert_array_equal(tok, tok_many[:len(tok)])
+        np.testing.assert_array_equal(tot, tot_many[:len(tot)])
+        for q in range(len(pre)):
+            t1, s1 = score(jet_synth.from_lists(pre[q:q + 1], cand[q:q + 1]))
+            c0, c1 = few.q_cand_offsets[q], few.q_cand_offsets[q + 1]
+            np.testing.assert_array_equal(t1, tok[few.cand_tok_offsets[c0]:few.cand_tok_offsets[c1]], err_msg=f"{PREFIX[q]}")
+            np.testing.assert_array_equal(s1, tot[c0:c1])
+    finally:
+        J.jet_model_free(m)
+    ref_tok, ref_sum = oracle.score_unshared(path, few)
+    # the 16-bit modes' tolerance per token and per candidate
+    assert np.max(np.abs(tok - ref_tok)) <= 2e-2
+    assert np.max(np.abs(tot - ref_sum)) <= 5e-2
