@@ -34,10 +34,13 @@
 
 namespace jetk {
 
+// SWAP: the MFMA operands change places, so that acc[i][j] holds the transposed
+// block: A's rows along its columns (lanes), B's rows along its rows.
 template <typename T, int BM_, int BN_, int WM_, int WN_, int LOAD_ = 0, int SWZ_ = 0, int NSTAGE_ = 2,
-          int CPR_ = 8>
+          int CPR_ = 8, int SWAP_ = 0>
 struct GCfg {
   using type = T;
+  static constexpr bool SWAP = SWAP_ != 0;
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, LOAD = LOAD_, SWZ = SWZ_;
   static constexpr int NSTAGE = NSTAGE_, CPR = CPR_;
   static constexpr int WAVES_M = BM / WM, WAVES_N = BN / WN, NWAVES = WAVES_M * WAVES_N;
@@ -184,6 +187,13 @@ __device__ __forceinline__ void tile_coords(int nt_m, int nt_n, int *tm, int *tn
 }
 
 template <class C>
+__device__ __forceinline__ void tile_mma(f32x16 &acc, const Frag<typename C::type> &a,
+                                         const Frag<typename C::type> &b) {
+  if constexpr (C::SWAP) mma32(acc, b, a);
+  else mma32(acc, a, b);
+}
+
+template <class C>
 __device__ __forceinline__ void zero_acc(f32x16 (&acc)[C::MI][C::NI]) {
 #pragma unroll
   for (int i = 0; i < C::MI; ++i)
@@ -216,7 +226,7 @@ __device__ __forceinline__ void tile_compute(const uint4 *__restrict__ lds, int 
 #pragma unroll
     for (int i = 0; i < C::MI; ++i)
 #pragma unroll
-      for (int j = 0; j < C::NI; ++j) mma32(acc[i][j], fa[i], fb[j]);
+      for (int j = 0; j < C::NI; ++j) tile_mma<C>(acc[i][j], fa[i], fb[j]);
   }
 }
 
@@ -253,7 +263,7 @@ __device__ __forceinline__ void kk_mma(const Frag<typename C::type> (&fa)[C::MI]
 #pragma unroll
   for (int i = 0; i < C::MI; ++i)
 #pragma unroll
-    for (int j = 0; j < C::NI; ++j) mma32(acc[i][j], fa[i], fb[j]);
+    for (int j = 0; j < C::NI; ++j) tile_mma<C>(acc[i][j], fa[i], fb[j]);
 }
 
 // ---------------------------------------------------------------------------

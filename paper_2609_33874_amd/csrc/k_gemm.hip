@@ -222,103 +222,110 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(GemmArgs<typename C::type> 
 }
 
 // LM head with online log-sum-exp (Section 3.1 Eq. 2 evaluated over vocabulary
-// tiles): logits^T = W[V x K] * F[R x K]^T tile by tile; each lane keeps a
-// running (max, sum of exp) in base 2 for its rows of F; one partial per
-// (row, vocabulary split) is written. The logits stay in registers.
-// F holds R rows of K columns: the final hidden rows, or (hi, lo) pairs of
-// them when K = 2 KW (W rows are then read twice).
+// tiles): logits = F[R x K] * W[V x K]^T tile by tile, transposed in the
+// accumulators (C::SWAP), so each lane owns rows of F: it keeps a running
+// (max, sum of exp) in base 2 for them, and one partial per (row, vocabulary
+// split) is written. The logits stay in registers. With pair operands F holds
+// (hi, lo) rows [hi (K) | lo (K)] and each W fragment serves both.
+// The tile of F rows (C::BM) follows the number of rows; a row's partials are
+// the same in every one of them (same vocabulary tiles, same order).
 // With target (one vocabulary index per row of F), the product of a row with
 // its target's W row is kept as well, zt[row] (unscaled): the very
 // accumulator the log-sum-exp takes in, written by the one lane that holds it.
 template <class C>
 __global__ __launch_bounds__(C::NT) void lmhead_lse_kernel(const typename C::type *__restrict__ W,
                                                           const typename C::type *__restrict__ F, int V, int R,
-                                                          int KW, int K, int tiles_per_split, float zscale,
+                                                          int K, int tiles_per_split, int nsplit, float zscale,
                                                           float *__restrict__ part_m, float *__restrict__ part_s,
                                                           const int32_t *__restrict__ target,
                                                           float *__restrict__ zt) {
   extern __shared__ uint4 lds[];
-  const int n0 = blockIdx.x * C::BN, split = blockIdx.y;
-  const int ntiles = (V + C::BM - 1) / C::BM;
+  // Workgroups go round-robin to the 8 XCDs: XCD x takes the splits x, x + 8,
+  // .., each with all its row tiles in a row, so a vocabulary tile is read
+  // into one L2 only.
+  const int nrt = (R + C::BM - 1) / C::BM;
+  const int seq = blockIdx.x >> 3, split = (seq / nrt) * 8 + (blockIdx.x & 7), m0 = (seq % nrt) * C::BM;
+  if (split >= nsplit) return;
+  const int ntiles = (V + C::BN - 1) / C::BN;
   const int vt0 = split * tiles_per_split, vt1 = min(vt0 + tiles_per_split, ntiles);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
-  float rm[C::NI], rs[C::NI];
-  int tj[C::NI];  // this lane's rows' targets (-1: none)
+  float rm[C::MI], rs[C::MI];
+  int tj[C::MI];  // this lane's rows' targets (-1: none)
 #pragma unroll
-  for (int j = 0; j < C::NI; ++j) {
-    rm[j] = -INFINITY;
-    rs[j] = 0.0f;
-    const int row = n0 + wn * C::WN + j * 32 + (lane & 31);
-    tj[j] = target && row < R ? target[row] : -1;
+  for (int i = 0; i < C::MI; ++i) {
+    rm[i] = -INFINITY;
+    rs[i] = 0.0f;
+    const int row = m0 + wm * C::WM + i * 32 + (lane & 31);
+    tj[i] = target && row < R ? target[row] : -1;
   }
   f32x16 acc[C::MI][C::NI];
   for (int vt = vt0; vt < vt1; ++vt) {
-    const int m0 = vt * C::BM;
-    gemm_tile<C>(W, KW, F, K, V, R, K, KW, K, m0, n0, lds, acc);
-    // element e of acc[i][j] is vocabulary index vb + 32 i + 8 (e / 4) + e % 4
-    const int vb = m0 + wm * C::WM + 4 * (lane >> 5);
+    const int n0 = vt * C::BN;
+    gemm_tile<C>(F, C::PAIRA ? 2 * K : K, W, K, R, V, K, K, K, m0, n0, lds, acc);
+    // element e of acc[i][j] is vocabulary index vb + 32 j + 8 (e / 4) + e % 4
+    const int vb = n0 + wn * C::WN + 4 * (lane >> 5);
 #pragma unroll
-    for (int j = 0; j < C::NI; ++j) {
-      const int dv = tj[j] - vb;
-      if (dv >= 0 && dv < 32 * C::MI && (dv & 4) == 0) {
-        const int row = n0 + wn * C::WN + j * 32 + (lane & 31);
+    for (int i = 0; i < C::MI; ++i) {
+      const int dv = tj[i] - vb;
+      if (dv >= 0 && dv < 32 * C::NI && (dv & 4) == 0) {
+        const int row = m0 + wm * C::WM + i * 32 + (lane & 31);
         float z = 0.0f;
 #pragma unroll
-        for (int i = 0; i < C::MI; ++i)
+        for (int j = 0; j < C::NI; ++j)
 #pragma unroll
-          for (int e = 0; e < 16; ++e) z = dv == 32 * i + 8 * (e >> 2) + (e & 3) ? acc[i][j][e] : z;
+          for (int e = 0; e < 16; ++e) z = dv == 32 * j + 8 * (e >> 2) + (e & 3) ? acc[i][j][e] : z;
         zt[row] = z;
       }
     }
 #pragma unroll
-    for (int j = 0; j < C::NI; ++j) {
+    for (int i = 0; i < C::MI; ++i) {
       float mx = -INFINITY;
 #pragma unroll
-      for (int i = 0; i < C::MI; ++i)
+      for (int j = 0; j < C::NI; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          const int v = m0 + wm * C::WM + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+          const int v = vb + 32 * j + 8 * (e >> 2) + (e & 3);
           const float z = v < V ? acc[i][j][e] * zscale : -INFINITY;
           acc[i][j][e] = z;
           mx = fmaxf(mx, z);
         }
       if (mx == -INFINITY) continue;
-      const float nm = fmaxf(rm[j], mx);
-      float s = rs[j] * exp2f(rm[j] - nm);
+      const float nm = fmaxf(rm[i], mx);
+      float s = rs[i] * exp2f(rm[i] - nm);
 #pragma unroll
-      for (int i = 0; i < C::MI; ++i)
+      for (int j = 0; j < C::NI; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) s += exp2f(acc[i][j][e] - nm);
-      rm[j] = nm;
-      rs[j] = s;
+      rm[i] = nm;
+      rs[i] = s;
     }
   }
-  // merge the two lane halves that hold the same column, then the waves
-  // along the vocabulary dimension through LDS
-  float *sm = reinterpret_cast<float *>(lds);  // [WAVES_M][BN] maxima, then sums
+  // merge the two lane halves that hold the same row, then the waves along
+  // the vocabulary dimension through LDS
+  float *sm = reinterpret_cast<float *>(lds);  // [WAVES_N][BM] maxima, then sums
 #pragma unroll
-  for (int j = 0; j < C::NI; ++j) {
-    const float om = __shfl_xor(rm[j], 32), os = __shfl_xor(rs[j], 32);
-    const float nm = fmaxf(rm[j], om);
+  for (int i = 0; i < C::MI; ++i) {
+    const float om = __shfl_xor(rm[i], 32), os = __shfl_xor(rs[i], 32);
+    const float nm = fmaxf(rm[i], om);
     float s = 0.0f;
-    if (nm != -INFINITY) s = rs[j] * exp2f(rm[j] - nm) + os * exp2f(om - nm);
+    if (nm != -INFINITY) s = rs[i] * exp2f(rm[i] - nm) + os * exp2f(om - nm);
     if (lane < 32) {
-      const int cl = wn * C::WN + j * 32 + lane;
-      sm[wm * C::BN + cl] = nm;
-      sm[C::WAVES_M * C::BN + wm * C::BN + cl] = s;
+      const int rl = wm * C::WM + i * 32 + lane;
+      sm[wn * C::BM + rl] = nm;
+      sm[C::WAVES_N * C::BM + wn * C::BM + rl] = s;
     }
   }
   __syncthreads();
-  for (int cl = threadIdx.x; cl < C::BN; cl += C::NT) {
-    const int row = n0 + cl;
+  for (int rl = threadIdx.x; rl < C::BM; rl += C::NT) {
+    const int row = m0 + rl;
     if (row >= R) continue;
     float M = -INFINITY;
-    for (int w = 0; w < C::WAVES_M; ++w) M = fmaxf(M, sm[w * C::BN + cl]);
+    for (int w = 0; w < C::WAVES_N; ++w) M = fmaxf(M, sm[w * C::BM + rl]);
     float S = 0.0f;
     if (M != -INFINITY)
-      for (int w = 0; w < C::WAVES_M; ++w)
-        S += sm[C::WAVES_M * C::BN + w * C::BN + cl] * exp2f(sm[w * C::BN + cl] - M);
+      for (int w = 0; w < C::WAVES_N; ++w)
+        S += sm[C::WAVES_N * C::BM + w * C::BM + rl] * exp2f(sm[w * C::BM + rl] - M);
     part_m[(int64_t)split * R + row] = M;
     part_s[(int64_t)split * R + row] = S;
   }
@@ -342,8 +349,6 @@ using PairB = GCfg<bf16, 256, 256, 64, 128, 7, 2, 3, 4>;
 using PairS = GCfg<bf16, 128, 128, 32, 64, 7, 2, 3, 4>;
 using SmallB = GCfg<bf16, 256, 128, 64, 64, 2, 1, 3, 8>;
 using CfgF = GCfg<float, 128, 128, 64, 64, 0, 1>;
-using LmB = GCfg<bf16, 256, 256, 128, 64, 4, 1, 2, 8>;
-using LmF = GCfg<float, 128, 128, 64, 64, 0, 1>;
 // fp16 operands: the LOAD 7 schedule with a single A plane (three 32 KB
 // stages of 32-column A and B tiles), 256x256 tiles with waves of 64 x 128,
 // or 128x128 tiles (the last round of a large launch, grouped GEMMs, and
@@ -359,7 +364,15 @@ using HalfM = GCfg<f16, 256, 128, 64, 64, 8, 2, 3, 4>;
 // (hi, lo) fp16 pair A operands: the bf16 pair schedules with fp16 operands
 using HalfPairB = GCfg<f16, 256, 256, 64, 128, 7, 2, 3, 4>;
 using HalfPairS = GCfg<f16, 128, 128, 32, 64, 7, 2, 3, 4>;
-using LmH = GCfg<f16, 256, 256, 64, 128, 8, 2, 3, 4>;
+// LM head: the 256x256 schedules transposed (F rows x 256 vocabulary rows), and
+// 64- and 128-row tiles of the same waves for few rows.
+template <typename T, bool PAIR>
+using Lm = GCfg<T, 256, 256, 64, 128, PAIR ? 7 : 8, 2, 3, 4, 1>;
+template <typename T, bool PAIR>
+using LmMid = GCfg<T, 128, 256, 64, 128, PAIR ? 7 : 8, 2, 3, 4, 1>;
+template <typename T, bool PAIR>
+using LmSmall = GCfg<T, 64, 256, 64, 128, PAIR ? 7 : 8, 2, 4, 4, 1>;
+using LmF = GCfg<float, 128, 128, 64, 64, 0, 1, 2, 8, 1>;
 // int8 B operand (block-quantized weights): the LOAD 8 schedule with int8 B
 // tiles and per-block scales (three 24.5 KB stages), 256x256 tiles of 8
 // waves, or 128x128 tiles of 4 waves for problems with fewer tiles.
@@ -675,25 +688,38 @@ void lmhead_plan(int dtype, int V, int R, int *tiles_per_split, int *nsplit) {
   // The split of the vocabulary depends on V only, so that a row's
   // log-sum-exp is merged in the same order whatever batch it is in; about
   // 256 splits keep even a one-row-tile launch spread over the CUs.
-  const int bm = dtype == 1 ? LmF::BM : LmB::BM;
-  const int vt = (V + bm - 1) / bm;
+  const int bn = dtype == 1 ? LmF::BN : Lm<f16, false>::BN;
+  const int vt = (V + bn - 1) / bn;
   const int tps = std::max(1, vt / 256);
   *tiles_per_split = tps;
   *nsplit = (vt + tps - 1) / tps;
 }
 
 template <class C>
-static hipError_t run_lmhead(const void *W, const void *F, int V, int R, int K, int pair, int tiles_per_split,
-                             float wscale, float *part_m, float *part_s, const int32_t *target, float *zt,
-                             hipStream_t st) {
+static hipError_t run_lmhead(const void *W, const void *F, int V, int R, int K, int tiles_per_split, float wscale,
+                             float *part_m, float *part_s, const int32_t *target, float *zt, hipStream_t st) {
   using T = typename C::type;
   static const hipError_t once = allow_lds<C>((const void *)lmhead_lse_kernel<C>);
   if (once != hipSuccess) return once;
-  const int nsplit = ((V + C::BM - 1) / C::BM + tiles_per_split - 1) / tiles_per_split;
-  dim3 grid((R + C::BN - 1) / C::BN, nsplit);
-  hipLaunchKernelGGL((lmhead_lse_kernel<C>), grid, dim3(C::NT), C::LDS_BYTES, st, (const T *)W, (const T *)F, V, R,
-                     K, pair ? 2 * K : K, tiles_per_split, wscale * kLog2e, part_m, part_s, target, zt);
+  const int nsplit = ((V + C::BN - 1) / C::BN + tiles_per_split - 1) / tiles_per_split;
+  const int nrt = (R + C::BM - 1) / C::BM;
+  hipLaunchKernelGGL((lmhead_lse_kernel<C>), dim3((nsplit + 7) / 8 * 8 * nrt), dim3(C::NT), C::LDS_BYTES, st,
+                     (const T *)W, (const T *)F, V, R, K, tiles_per_split, nsplit, wscale * kLog2e, part_m, part_s,
+                     target, zt);
   return hipGetLastError();
+}
+
+// The row tile: the fewest rounds of full tiles. 64 rows and 128 rows are
+// bound by the stream of W, not by the matrix cores.
+template <typename T, bool PAIR>
+static hipError_t run_lmhead_rows(const void *W, const void *F, int V, int R, int K, int tiles_per_split,
+                                  float wscale, float *part_m, float *part_s, const int32_t *target, float *zt,
+                                  hipStream_t st) {
+  if (R <= 64)
+    return run_lmhead<LmSmall<T, PAIR>>(W, F, V, R, K, tiles_per_split, wscale, part_m, part_s, target, zt, st);
+  if (R <= 128)
+    return run_lmhead<LmMid<T, PAIR>>(W, F, V, R, K, tiles_per_split, wscale, part_m, part_s, target, zt, st);
+  return run_lmhead<Lm<T, PAIR>>(W, F, V, R, K, tiles_per_split, wscale, part_m, part_s, target, zt, st);
 }
 
 hipError_t launch_lmhead_lse(int dtype, const void *W, const void *F, int V, int R, int K, int pair,
@@ -701,10 +727,11 @@ hipError_t launch_lmhead_lse(int dtype, const void *W, const void *F, int V, int
                              float *zt, hipStream_t st) {
   if (R <= 0) return hipSuccess;
   if ((target == nullptr) != (zt == nullptr)) return hipErrorInvalidValue;
-  if (dtype == 0)
-    return run_lmhead<LmB>(W, F, V, R, K, pair, tiles_per_split, wscale, part_m, part_s, target, zt, st);
-  if (dtype == 2) return run_lmhead<LmH>(W, F, V, R, K, 0, tiles_per_split, wscale, part_m, part_s, target, zt, st);
-  return run_lmhead<LmF>(W, F, V, R, K, 0, tiles_per_split, wscale, part_m, part_s, target, zt, st);
+  if (dtype == 1) return run_lmhead<LmF>(W, F, V, R, K, tiles_per_split, wscale, part_m, part_s, target, zt, st);
+  if (dtype == 2)
+    return run_lmhead_rows<f16, false>(W, F, V, R, K, tiles_per_split, wscale, part_m, part_s, target, zt, st);
+  return pair ? run_lmhead_rows<bf16, true>(W, F, V, R, K, tiles_per_split, wscale, part_m, part_s, target, zt, st)
+              : run_lmhead_rows<bf16, false>(W, F, V, R, K, tiles_per_split, wscale, part_m, part_s, target, zt, st);
 }
 
 }  // namespace jetk

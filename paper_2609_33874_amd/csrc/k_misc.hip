@@ -137,16 +137,30 @@ __global__ __launch_bounds__(256) void rope_scatter_kernel(const float *__restri
   }
 }
 
+// Log-sum-exp of a row from its partials over the vocabulary splits: 8 rows
+// per workgroup, 32 lanes of splits per row, each lane its splits in ascending
+// order, then the lanes in order. One thread per row walking the splits
+// alone took 145 us for 63 rows of 297 splits (a chain of loads on one CU).
 __global__ __launch_bounds__(256) void lse_merge_kernel(const float *__restrict__ pm, const float *__restrict__ ps,
                                                          int nsplit, int R, float *__restrict__ lse,
                                                          const float *__restrict__ zt, float wscale,
                                                          float *__restrict__ ell) {
-  const int r = blockIdx.x * 256 + threadIdx.x;
-  if (r >= R) return;
+  __shared__ float sm[32][8], ss[32][8];
+  const int rl = threadIdx.x & 7, sl = threadIdx.x >> 3, r = blockIdx.x * 8 + rl;
   float M = -INFINITY;
-  for (int s = 0; s < nsplit; ++s) M = fmaxf(M, pm[(int64_t)s * R + r]);
+  if (r < R)
+    for (int s = sl; s < nsplit; s += 32) M = fmaxf(M, pm[(int64_t)s * R + r]);
+  sm[sl][rl] = M;
+  __syncthreads();
+  for (int s = 0; s < 32; ++s) M = fmaxf(M, sm[s][rl]);
   float S = 0.0f;
-  for (int s = 0; s < nsplit; ++s) S += ps[(int64_t)s * R + r] * exp2f(pm[(int64_t)s * R + r] - M);
+  if (r < R)
+    for (int s = sl; s < nsplit; s += 32) S += ps[(int64_t)s * R + r] * exp2f(pm[(int64_t)s * R + r] - M);
+  ss[sl][rl] = S;
+  __syncthreads();
+  if (sl != 0 || r >= R) return;
+  S = 0.0f;
+  for (int s = 0; s < 32; ++s) S += ss[s][rl];
   const float l = (M + log2f(S)) * kLn2;
   lse[r] = l;
   if (zt) ell[r] = zt[r] * wscale - l;
@@ -286,7 +300,7 @@ hipError_t launch_lse_merge(const float *pm, const float *ps, int nsplit, int R,
                             float wscale, float *ell, hipStream_t st) {
   if (R <= 0) return hipSuccess;
   if (zt && !ell) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(lse_merge_kernel, dim3((R + 255) / 256), dim3(256), 0, st, pm, ps, nsplit, R, lse, zt, wscale,
+  hipLaunchKernelGGL(lse_merge_kernel, dim3((R + 7) / 8), dim3(256), 0, st, pm, ps, nsplit, R, lse, zt, wscale,
                      ell);
   return hipGetLastError();
 }
