@@ -1,4 +1,8 @@
-// Grouped-query attention on matrix cores for gfx950.
+// Grouped-query attention on matrix cores for gfx950: fp32, (hi, lo) pairs, and
+// single 16-bit planes with head_dim 32 or 64 (k_attn16.hip runs 128; with
+// pairs its two stages fill the LDS of a CU, and one workgroup per CU measured
+// 25% slower than two of this kernel: 3.20 against 2.57 ms, 27B prefix of
+// 16,868 rows).
 //
 // One workgroup (4 waves) takes up to 64 query slots of one (question, KV
 // head): slot s is query head kvh * G + s % G at row s / G, so the G query
@@ -23,24 +27,9 @@
 // PAIR: q, K, V and the output are (hi, lo) bf16 pairs (value = hi + lo);
 // products use hi*hi + lo*hi + hi*lo (the lo*lo term is below fp32 rounding
 // of the sum), and the probabilities are split into a pair the same way.
-#include "device.h"
-#include "kernels.h"
+#include "attn_common.h"
 
 namespace jetk {
-
-template <typename T> __device__ __forceinline__ Frag<T> pack8(const float (&x)[8]) {
-  static_assert(sizeof(T) == 2, "16-bit types");
-  Frag<T> f;
-  const uint4 u = make_uint4(pack2<T>(x[0], x[1]), pack2<T>(x[2], x[3]), pack2<T>(x[4], x[5]), pack2<T>(x[6], x[7]));
-  f.v = __builtin_bit_cast(typename Vec8<T>::type, u);
-  return f;
-}
-template <> __device__ __forceinline__ Frag<float> pack8<float>(const float (&x)[8]) {
-  Frag<float> f;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) f.v[j] = x[j];
-  return f;
-}
 
 template <typename T>
 __device__ __forceinline__ void lds_kfrag(Frag<T> &f, const uint4 *row, int c0, int swz) {
@@ -439,7 +428,14 @@ constexpr int attn_qb() {
   return sizeof(T) == 2 && !PAIR ? 2 : 1;
 }
 
-int attn_slots_per_item(int dtype, int pair) { return (dtype == 1 || pair) ? 64 : 128; }
+// 128 slots: each staged tile and each K / V fragment read from LDS serves
+// twice the queries of 64. 64 where the registers hold no more (pairs, fp32),
+// where most of a 128-slot item would be idle, and where the 128-slot items
+// would leave half of the CUs without one.
+int attn_block(int dtype, int pair, int mode, double slots, double total) {
+  if (dtype == 1 || pair || (mode == 1 && slots < 96.0)) return 64;
+  return total < 128.0 * 128.0 ? 64 : 128;
+}
 
 template <typename T, int HD, bool PAIR, int QB>
 static hipError_t run_attn_qb(const AttnArgs &a, hipStream_t st) {
@@ -452,21 +448,21 @@ template <typename T, int HD, bool PAIR>
 static hipError_t run_attn(const AttnArgs &a, hipStream_t st) {
   constexpr int QB = attn_qb<T, PAIR>();
   if (a.n_items <= 0) return hipSuccess;
-  if (a.qb < 1 || a.qb > QB) return hipErrorInvalidValue;
+  if (a.block != 64 && a.block != 64 * QB) return hipErrorInvalidValue;
   if constexpr (QB == 2) {
-    if (a.qb == 2) return run_attn_qb<T, HD, PAIR, 2>(a, st);
+    if (a.block == 128) return run_attn_qb<T, HD, PAIR, 2>(a, st);
   }
   return run_attn_qb<T, HD, PAIR, 1>(a, st);
 }
 
 hipError_t launch_attention(int dtype, const AttnArgs &a, hipStream_t st) {
+  if (attn16_ok(dtype, a.pair, a.hd)) return launch_attn16(dtype, a, st);
   if (dtype == 0) {
     if (a.pair) {
       if (a.hd == 128) return run_attn<bf16, 128, true>(a, st);
       if (a.hd == 64) return run_attn<bf16, 64, true>(a, st);
       if (a.hd == 32) return run_attn<bf16, 32, true>(a, st);
     } else {
-      if (a.hd == 128) return run_attn<bf16, 128, false>(a, st);
       if (a.hd == 64) return run_attn<bf16, 64, false>(a, st);
       if (a.hd == 32) return run_attn<bf16, 32, false>(a, st);
     }
@@ -477,7 +473,6 @@ hipError_t launch_attention(int dtype, const AttnArgs &a, hipStream_t st) {
       if (a.hd == 32) return run_attn<f16, 32, true>(a, st);
       return hipErrorInvalidValue;
     }
-    if (a.hd == 128) return run_attn<f16, 128, false>(a, st);
     if (a.hd == 64) return run_attn<f16, 64, false>(a, st);
     if (a.hd == 32) return run_attn<f16, 32, false>(a, st);
   } else {

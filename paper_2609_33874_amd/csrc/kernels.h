@@ -73,7 +73,7 @@ hipError_t launch_lse_merge(const float *part_m, const float *part_s, int nsplit
                             const float *zt, float wscale, float *ell, hipStream_t st);
 
 // Attention work item: one (question, kv head, block of at most
-// attn_slots_per_item query slots).
+// AttnArgs::block query slots).
 struct AttnItem {
   int32_t q, kvh, slot0, nslots, nkeys_pre;
 };
@@ -108,15 +108,18 @@ struct AttnArgs {
   AttnQuestions qs;
   const AttnItem *items;
   int n_items;
-  int qb;  // blocks of 16 query slots per wave the items were built for: 64 qb slots per item
+  int block;  // query slots per item the items were built for (attn_block)
   int Hq, Hkv, hd;
   float scale;
 };
 hipError_t launch_attention(int dtype, const AttnArgs &a, hipStream_t st);
-// Largest query-slot count per work item launch_attention supports (64 or
-// 128); the items of a launch hold at most 64 * AttnArgs::qb slots, qb being
-// 1 or, where this returns 128, 2.
-int attn_slots_per_item(int dtype, int pair);
+// Query slots per work item for a launch whose questions have `slots` query
+// slots per KV head on average and `total` in all (over questions and KV
+// heads). A query's arithmetic does not depend on it.
+int attn_block(int dtype, int pair, int mode, double slots, double total);
+// The kernel for single 16-bit planes and head_dim 128 (k_attn16.hip).
+inline bool attn16_ok(int dtype, int pair, int hd) { return dtype != 1 && !pair && hd == 128; }
+hipError_t launch_attn16(int dtype, const AttnArgs &a, hipStream_t st);
 
 // Gated delta-rule layers. Projection output x [R][ldx] = q~ (H dk) | k~ (H dk)
 // | v~ (H dv) | z (H dv) | b (H) | a (H), fp32. hist[3 r + j - 1] names the
