@@ -73,13 +73,28 @@ template <class C, int EPI>
 __device__ __forceinline__ int small_col(int wn, int j) {
   if constexpr (EPI == 2 && C::NI % 4 == 0) return wn * 16 * C::NI + (j >> 2) * 64 + (j & 1) * 32 + ((j >> 1) & 1) * 16;
   else if constexpr (EPI == 2) return (wn >> 1) * 64 + (wn & 1) * 16 + j * 32;
-  else if constexpr (EPI == 4) return (wn >> 2) * 128 + (wn & 3) * 16 + j * 64;
+  else if constexpr (EPI == 4 && !(C::BN == 32)) return (wn >> 2) * 128 + (wn & 3) * 16 + j * 64;
   else return (wn * C::NI + j) * 16;
 }
 
 // acc += A[m0 ..][K] * B[n0 ..][K]^T over a workgroup's tile. ldb and the
 // byte layout of a quantized B as in launch_gemm_q8 / _q4. Needs K a multiple
 // of BK and K / BK >= NS - 1. Rows past M / N load the last valid row.
+// RoPE tiles of 32 columns: 16 dims d and the 16 dims d + 64 of one head (four
+// tiles per head), so that few rows still spread over many CUs.
+template <class C, int EPI>
+constexpr bool small_split = EPI == 4 && C::BN == 32;
+
+// First column of tile tn of B, and the column of the tile's LDS row r past it.
+template <class C, int EPI>
+__device__ __forceinline__ int small_n0(int tn) {
+  return small_split<C, EPI> ? (tn >> 2) * 128 + (tn & 3) * 16 : tn * C::BN;
+}
+template <class C, int EPI>
+__device__ __forceinline__ int small_row(int r) {
+  return small_split<C, EPI> ? (r & 15) + (r >> 4) * 64 : r;
+}
+
 // Swizzle of the 16-byte chunks of a row of CH chunks: the 16 rows that a
 // fragment read touches at one logical chunk spread over all banks.
 template <int CH>
@@ -111,7 +126,7 @@ __device__ __forceinline__ void small_tile(const typename C::type *__restrict__ 
 #pragma unroll
   for (int i = 0; i < C::B_LD; ++i) {
     const int u = (i * C::NW + wave) * 64 + lane, r = u / CB, c = (u % CB) ^ small_swz<CB>(r);
-    pb[i] = B + (int64_t)min(n0 + r, N - 1) * ldb_bytes + c * 16;
+    pb[i] = B + (int64_t)min(n0 + small_row<C, EPI>(r), N - 1) * ldb_bytes + c * 16;
   }
   const char *ps = nullptr;  // scales: 256 bytes per (K block of 32, row group of 128); 4 blocks per K step
   int64_t s_step = 0;
@@ -169,7 +184,7 @@ __device__ __forceinline__ void small_tile(const typename C::type *__restrict__ 
           if constexpr (C::QB == 8)
             rb[h][k][j] = *(const uint2 *)(b + r * 128 + (((kk * 2 + (g >> 1)) ^ small_swz<CB>(r16)) << 4) + (g & 1) * 8);
           else rb[h][k][j].x = *(const uint32_t *)(b + r * 64 + ((kk ^ small_swz<CB>(r16)) << 4) + g * 4);
-          const int n = (n0 & 127) + r;
+          const int n = (n0 & 127) + small_row<C, EPI>(r);
           sb[h][k][j] = *(const uint16_t *)(b + C::B_BYTES + kk * 256 + (n & 31) * 8 + (n >> 5) * 2);
         }
       }
@@ -233,7 +248,7 @@ __global__ __launch_bounds__(C::NT) void gemm_small_kernel(GemmArgs<typename C::
   const int nt_m = (g.M + C::BM - 1) / C::BM, nt_n = (g.N + C::BN - 1) / C::BN;
   int tm, tn;
   tile_coords(nt_m, nt_n, &tm, &tn);
-  const int m0 = tm * C::BM, n0 = tn * C::BN;
+  const int m0 = tm * C::BM, n0 = small_n0<C, EPI>(tn);
   const T *B = g.B;
   if (g.tile_group) {
     const int grp = g.tile_group[tm];
@@ -262,7 +277,7 @@ __global__ __launch_bounds__(C::NT) void gemm_small_kernel(GemmArgs<typename C::
           put_split<T>((T *)g.out + (int64_t)row * g.ldo + f, g.N >> 1, v, g.pair_out);
         }
       } else if constexpr (EPI == 4) {
-        static_assert(C::NI == 2 && C::WGN % 4 == 0, "dims d and d + 64 of a head per wave");
+        static_assert(C::NI == 2 && (small_split<C, 4> || C::WGN % 4 == 0), "dims d and d + 64 of a head per wave");
         const QkvRope &q = g.rope;
         const int head = (n0 >> 7) + (wn >> 2);  // query heads, then key heads, then value heads
         if (head >= q.Hq + 2 * q.Hkv) continue;
@@ -271,7 +286,7 @@ __global__ __launch_bounds__(C::NT) void gemm_small_kernel(GemmArgs<typename C::
         if (head < q.Hq) dst = (T *)q.q_out + ((int64_t)row * q.Hq + head) * 128;
         else if (head < q.Hq + q.Hkv) dst = (T *)q.k_cache + ((int64_t)(head - q.Hq) * q.S + q.slot0 + row) * 128;
         else dst = (T *)q.v_cache + ((int64_t)(head - q.Hq - q.Hkv) * q.S + q.slot0 + row) * 128;
-        const int d = (wn & 3) * 16 + (lane & 15);
+        const int d = (small_split<C, 4> ? n0 & 63 : (wn & 3) * 16) + (lane & 15);
         const float x1 = acc[i][0][e] * g.oscale, x2 = acc[i][1][e] * g.oscale;
         if (head < q.Hq + q.Hkv) {
           const int64_t p = q.pos[row];

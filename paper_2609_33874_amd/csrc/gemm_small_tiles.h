@@ -77,8 +77,11 @@ struct SmallRope<T, 1, 0> {
   using c0 = SCfg<T, 1, 0, 1, 2, 1, 4, 4>;      // 16 x 128
   using c1 = SCfg<T, 1, 0, 2, 2, 2, 4, 3>;      // 64 x 128
   using c2 = SCfg<T, 1, 0, 4, 2, 2, 4, 5, 64>;  // 128 x 128
-  using types = TileTypes<c0, c1, c2>;
-  static constexpr TileCost cost[] = {tile_cost<c0>(2.5, 4.4), tile_cost<c1>(4.0, 5.4), tile_cost<c2>(8.0, 7.8)};
+  using c3 = SCfg<T, 1, 0, 1, 2, 2, 1, 8>;      // 32 x 32
+  using c4 = SCfg<T, 1, 0, 1, 2, 4, 1, 6>;      // 64 x 32
+  using types = TileTypes<c0, c1, c2, c3, c4>;
+  static constexpr TileCost cost[] = {tile_cost<c0>(2.5, 4.4), tile_cost<c1>(4.0, 5.4), tile_cost<c2>(8.0, 7.8),
+                                      tile_cost<c3>(2.2, 2.1), tile_cost<c4>(2.2, 2.9)};
 };
 
 template <typename T>
@@ -105,8 +108,10 @@ struct SmallRope<T, 2, 0> {
   using c0 = SCfg<T, 2, 0, 1, 2, 1, 4, 3>;      // 16 x 128
   using c1 = SCfg<T, 2, 0, 2, 2, 2, 4, 5, 64>;  // 64 x 128
   using c2 = SCfg<T, 2, 0, 4, 2, 2, 4, 3, 64>;  // 128 x 128
-  using types = TileTypes<c0, c1, c2>;
-  static constexpr TileCost cost[] = {tile_cost<c0>(2.0, 5.8), tile_cost<c1>(3.0, 8.0), tile_cost<c2>(9.0, 13.3)};
+  using c3 = SCfg<T, 2, 0, 1, 2, 2, 1, 6>;      // 32 x 32
+  using types = TileTypes<c0, c1, c2, c3>;
+  static constexpr TileCost cost[] = {tile_cost<c0>(2.0, 5.8), tile_cost<c1>(3.0, 8.0), tile_cost<c2>(9.0, 13.3),
+                                      tile_cost<c3>(1.8, 3.6)};
 };
 
 // Block-quantized B: a tile holds one row group of scales, 64 or 128 columns.
@@ -129,7 +134,15 @@ struct SmallSwiglu<T, 1, QB> {
   static constexpr TileCost cost[] = {tile_cost<c0>(2.5, 4.4), tile_cost<c1>(4.0, 5.6), tile_cost<c2>(5.0, 9.0)};
 };
 template <typename T, int QB>
-struct SmallRope<T, 1, QB> : SmallSwiglu<T, 1, QB> {};
+struct SmallRope<T, 1, QB> {
+  using c0 = SCfg<T, 1, QB, 1, 2, 1, 4, 5>;  // 16 x 128
+  using c1 = SCfg<T, 1, QB, 2, 2, 2, 4, 4>;  // 64 x 128
+  using c2 = SCfg<T, 1, QB, 4, 2, 2, 4, 3>;  // 128 x 128
+  using c3 = SCfg<T, 1, QB, 1, 2, 2, 1, 8>;  // 32 x 32
+  using types = TileTypes<c0, c1, c2, c3>;
+  static constexpr TileCost cost[] = {tile_cost<c0>(2.5, 4.4), tile_cost<c1>(4.0, 5.6), tile_cost<c2>(5.0, 9.0),
+                                      tile_cost<c3>(2.2, 2.3)};
+};
 
 template <typename T, int NPL, int QB>
 hipError_t run_small_tiles(int epi, int cfg, const GemmArgs<T> &g, hipStream_t st) {

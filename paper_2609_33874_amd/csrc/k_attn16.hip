@@ -192,44 +192,50 @@ __global__ __launch_bounds__(64 * NW, 2) void attn16_kernel(AttnArgs a) {
       const uint32_t so = (uint32_t)(stage * STAGE);
       f32x4 s[QB][4];
       Frag<T> fk[2][4];
-      auto read_k = [&](int kb, Frag<T> (&f)[4]) {
+      auto read_k = [&](int ks, int kb, Frag<T> &f) { ds_read16<0>(f.v, koff[ks] + so + kb * 4096); };
+      auto score = [&](int ks, int kb, Frag<T> &f) {
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) ds_read16<0>(f[ks].v, koff[ks] + so + kb * 4096);
+        for (int qb = 0; qb < QB; ++qb) mma16(s[qb][kb], f, qf[qb][ks]);
       };
-      auto score = [&](int kb, Frag<T> (&f)[4]) {
+      auto arrived = [&](Frag<T> (&f)[4]) {
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) asm volatile("" : "+v"(f[ks].v));
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-          for (int qb = 0; qb < QB; ++qb) mma16(s[qb][kb], f[ks], qf[qb][ks]);
-        __builtin_amdgcn_sched_barrier(0);
+        for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(f[i].v));
       };
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) s[qb][kb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
       if (nk > 48) {
-        // 16 keys at a time, the next ones' reads ahead (no read is in flight
-        // across a branch: the compiler must not get to copy its registers)
-        read_k(0, fk[0]);
+        // 32 dims at a time over all four key blocks (four independent chains
+        // of MFMAs), the next ones' reads ahead. No read is in flight across a
+        // branch: the compiler must not get to copy its registers.
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb) {
-          if (kb < 3) {
-            read_k(kb + 1, fk[(kb + 1) & 1]);
+        for (int kb = 0; kb < 4; ++kb) read_k(0, kb, fk[0][kb]);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+          if (ks < 3) {
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb) read_k(ks + 1, kb, fk[(ks + 1) & 1][kb]);
             wait_lgkmcnt<4>();
           } else {
             wait_lgkmcnt<0>();
           }
-          score(kb, fk[kb & 1]);
+          arrived(fk[ks & 1]);
+#pragma unroll
+          for (int kb = 0; kb < 4; ++kb) score(ks, kb, fk[ks & 1][kb]);
+          __builtin_amdgcn_sched_barrier(0);
         }
       } else {
 #pragma unroll
         for (int kb = 0; kb < 3; ++kb)
           if (kb * 16 < nk) {
-            read_k(kb, fk[0]);
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) read_k(ks, kb, fk[0][ks]);
             wait_lgkmcnt<0>();
-            score(kb, fk[0]);
+            arrived(fk[0]);
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) score(ks, kb, fk[0][ks]);
+            __builtin_amdgcn_sched_barrier(0);
           }
       }
       Frag<T> pf[QB][2];

@@ -60,12 +60,18 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_kernel(const float *__restri
   const float4 *xr = reinterpret_cast<const float4 *>(x + src * d);
   const float4 *g4 = reinterpret_cast<const float4 *>(g);
   const int n4 = d >> 2;
-  float4 v[NV];
+  float4 v[NV], gv[NV];
   float ss = 0.0f;
+  // the gains are loaded with the row, not after its sum: few rows are bound
+  // by the latency of these loads
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
     const int i = j * 64 + lane;
     v[j] = i < n4 ? xr[i] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    gv[j] = i < n4 ? g4[i] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  }
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
     ss += v[j].x * v[j].x + v[j].y * v[j].y + v[j].z * v[j].z + v[j].w * v[j].w;
   }
   ss = warp_sum(ss);
@@ -75,7 +81,7 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_kernel(const float *__restri
   for (int j = 0; j < NV; ++j) {
     const int i = j * 64 + lane;
     if (i >= n4) break;
-    const float4 gg = g4[i];
+    const float4 gg = gv[j];
     const float y[4] = {v[j].x * inv * gg.x, v[j].y * inv * gg.y, v[j].z * inv * gg.z, v[j].w * inv * gg.w};
     if constexpr (sizeof(T) == 4) {
       *reinterpret_cast<float4 *>(o + 4 * i) = make_float4(y[0], y[1], y[2], y[3]);
