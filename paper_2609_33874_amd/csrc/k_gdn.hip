@@ -125,14 +125,24 @@ __global__ __launch_bounds__(256) void gdn_conv_kernel(GdnConvArgs g, int R) {
   }
 }
 
-// One workgroup of 128 threads per (sequence, head); thread i owns state row
-// i (dv = dk = 128 values in registers). Steps are walked in order; k and q of
-// 32 steps at a time are staged in LDS. Every product with k or q takes the
-// element from a neighbouring lane instead of a private copy: each row of 16
-// lanes loads the step's k and q once, lane n holding elements 8n .. 8n + 7,
-// and an FMA reads element j from lane j / 8 of its row through the DPP
-// row_newbcast operand modifier (16-byte LDS reads per step: 4 instead of 96
-// workgroup-wide broadcasts, which bounded the kernel by LDS bandwidth).
+// Stepwise recurrence: one workgroup of 512 threads per (sequence, head). The
+// 128 x 128 state stays in registers, four threads per state row i (dv): thread
+// (i, c) holds the 32 elements j with j % 4 = c. The four partial sums of a
+// row's products with k and q are then one chain per thread, and the row sum
+// is (p0 + p1) + (p2 + p3), two exchanges away.
+//
+// What bounds it: steps are walked in order, so the time is the longest
+// sequence's steps times the latency of one. With one thread per row a step
+// took 384 FMAs in one wave and waited for its row of v from memory, 1.77 us
+// a step (24 sequences of 200 to 1500 steps, 16 heads: 2.65 ms a launch); the
+// four-way split runs 96 FMAs per thread and stages k, q, v, alpha and beta of
+// 32 steps at a time, the next 32 loaded while these are walked: 1.26 ms. 92
+// candidates of 1 to 24 steps: 67 us and 59.
+//
+// A wave holds 16 rows x 4 parts, part c in lanes 16 c .. 16 c + 15: an FMA
+// takes its element of k or q from a lane of its own 16 through the DPP
+// row_newbcast operand modifier, so lane n of part c keeps only elements
+// 8 n + c and 8 n + 4 + c of a step's k and q (one LDS read each).
 //
 // The state is held as S = c X with a scalar c (uniform over the workgroup),
 // so the decay S <- alpha S costs one multiply of c instead of one per state
@@ -143,91 +153,169 @@ __global__ __launch_bounds__(256) void gdn_conv_kernel(GdnConvArgs g, int R) {
 // within 2^40 of S, and a vanishing alpha is applied to X directly.
 constexpr int GDN_D = 128;
 constexpr int GDN_CHUNK = 32;
+constexpr int GDN_PART = GDN_D / 4;  // state elements per thread
 
-// acc += (x taken from lane N of this lane's row of 16) * b
-template <int N>
-__device__ __forceinline__ void fmac_rowbc(float &acc, float x, float b) {
-  asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(x), "v"(b), "n"(N));
+// p += s[m] k[m] for m = M .. M + 7, k[m] = kk[m % 2] of lane m / 2 of this
+// lane's 16. One block of inline asm: between single instructions the compiler
+// puts a wait state each. (The leading one covers a k just written by a VALU
+// instruction, which a DPP operand must be two wait states away from.)
+template <int M>
+__device__ __forceinline__ void gdn_dot8(const float (&s)[GDN_PART], const float (&kk)[2], float &p) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f32_dpp %0, %1, %3 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %2, %4 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %1, %5 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %2, %6 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %1, %7 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %2, %8 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %1, %9 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %2, %10 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+      : "+v"(p)
+      : "v"(kk[0]), "v"(kk[1]), "v"(s[M]), "v"(s[M + 1]), "v"(s[M + 2]), "v"(s[M + 3]), "v"(s[M + 4]), "v"(s[M + 5]),
+        "v"(s[M + 6]), "v"(s[M + 7]), "n"(M / 2), "n"(M / 2 + 1), "n"(M / 2 + 2), "n"(M / 2 + 3));
+}
+// s[m] += e k[m], then p += s[m] q[m], for m = M .. M + 3
+template <int M>
+__device__ __forceinline__ void gdn_update4(float (&s)[GDN_PART], const float (&kk)[2], const float (&qq)[2], float e,
+                                            float &p) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f32_dpp %1, %5, %9 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %7, %1 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %6, %9 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %8, %2 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %5, %9 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %7, %3 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %4, %6, %9 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %8, %4 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      : "+v"(p), "+v"(s[M]), "+v"(s[M + 1]), "+v"(s[M + 2]), "+v"(s[M + 3])
+      : "v"(kk[0]), "v"(kk[1]), "v"(qq[0]), "v"(qq[1]), "v"(e), "n"(M / 2), "n"(M / 2 + 1));
+}
+template <int... B>
+__device__ __forceinline__ void gdn_dot(const float (&s)[GDN_PART], const float (&kk)[2], float &p,
+                                        std::integer_sequence<int, B...>) {
+  (gdn_dot8<8 * B>(s, kk, p), ...);
+}
+template <int... B>
+__device__ __forceinline__ void gdn_update_dot(float (&s)[GDN_PART], const float (&kk)[2], const float (&qq)[2],
+                                               float e, float &p, std::integer_sequence<int, B...>) {
+  (gdn_update4<4 * B>(s, kk, qq, e, p), ...);
 }
 
-// p[j % 4] += s[j] k[j] (k[j] = kk[j % 8] of lane j / 8)
-template <int... J>
-__device__ __forceinline__ void gdn_dot(const float (&s)[GDN_D], const float (&kk)[8], float (&p)[4],
-                                        std::integer_sequence<int, J...>) {
-  (fmac_rowbc<J / 8>(p[J % 4], kk[J % 8], s[J]), ...);
+// (p0 + p1) + (p2 + p3) over the four parts of a row (lanes l, l ^ 16, l ^ 32, l ^ 48)
+__device__ __forceinline__ float gdn_row_sum(float p) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(p), __float_as_uint(p), false, false);
+  p = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(p), __float_as_uint(p), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-// s[j] += e k[j], then p[j % 4] += s[j] q[j] (k[j], q[j] from lane j / 8)
-template <int... J>
-__device__ __forceinline__ void gdn_update_dot(float (&s)[GDN_D], const float (&kk)[8], const float (&qq)[8], float e,
-                                               float (&p)[4], std::integer_sequence<int, J...>) {
-  ((fmac_rowbc<J / 8>(s[J], kk[J % 8], e), fmac_rowbc<J / 8>(p[J % 4], qq[J % 8], s[J])), ...);
-}
-
-__global__ __launch_bounds__(128) void gdn_recur_kernel(GdnRecurArgs g) {
-  __shared__ float4 ks[GDN_CHUNK][GDN_D / 4], qs[GDN_CHUNK][GDN_D / 4];
+__global__ __launch_bounds__(512) void gdn_recur_kernel(GdnRecurArgs g) {
+  constexpr int NT = 512, C4 = GDN_D / 4, PF = GDN_CHUNK * C4 / NT;  // f32x4 per thread and array of a chunk
+  // k, q, v and o of 32 steps; before and after, the whole state
+  __shared__ f32x4 sh[4 * GDN_CHUNK * C4];
+  f32x4(*ks)[C4] = reinterpret_cast<f32x4(*)[C4]>(sh), (*qs)[C4] = ks + GDN_CHUNK, (*vs)[C4] = qs + GDN_CHUNK,
+      (*os)[C4] = vs + GDN_CHUNK;
   __shared__ float al[GDN_CHUNK], be[GDN_CHUNK];
   const int H = g.H;
   const int si = blockIdx.x / H, h = blockIdx.x % H;
   const GdnSeq sq = g.seqs[si];
-  const int i = threadIdx.x, ln = i & 15;
-  float s[GDN_D];
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, c = lane >> 4;
+  const int i = (tid >> 6) * 16 + n;  // state row
+  float s[GDN_PART];
+  // The state comes and goes through the LDS in 16-byte pieces, piece x of row
+  // r at x ^ (r mod 32) (a candidate runs a few steps, so its time is mostly
+  // this).
+  constexpr int SP = GDN_D * C4 / NT;
+  const float *mine = reinterpret_cast<const float *>(sh) + i * GDN_D + c;
   if (sq.init >= 0) {
-    const float4 *src = reinterpret_cast<const float4 *>(g.S_init + (((int64_t)sq.init * H + h) * GDN_D + i) * GDN_D);
+    const f32x4 *src = reinterpret_cast<const f32x4 *>(g.S_init) + ((int64_t)sq.init * H + h) * GDN_D * C4;
+    f32x4 t[SP];
 #pragma unroll
-    for (int c = 0; c < GDN_D / 4; ++c) {
-      const float4 t = src[c];
-      s[4 * c] = t.x; s[4 * c + 1] = t.y; s[4 * c + 2] = t.z; s[4 * c + 3] = t.w;
+    for (int f = 0; f < SP; ++f) t[f] = src[f * NT + tid];
+#pragma unroll
+    for (int f = 0; f < SP; ++f) {
+      const int e = f * NT + tid, r = e / C4, x = e % C4;
+      sh[r * C4 + (x ^ (r & 31))] = t[f];
     }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < GDN_PART; ++m) s[m] = mine[4 * (m ^ (i & 31))];
   } else {
 #pragma unroll
-    for (int c = 0; c < GDN_D; ++c) s[c] = 0.0f;
+    for (int m = 0; m < GDN_PART; ++m) s[m] = 0.0f;
   }
+  // a chunk's rows of k, q and v (steps past the end repeat the last one)
+  f32x4 kr[PF], qr[PF], vr[PF];
+  float ar = 0.0f, br = 0.0f;
+  auto fetch = [&](int t0) {
+#pragma unroll
+    for (int f = 0; f < PF; ++f) {
+      const int e = f * NT + tid, tt = e / C4, x = e % C4;
+      const int64_t at = ((int64_t)(sq.row0 + min(t0 + tt, sq.len - 1)) * H + h) * C4 + x;
+      kr[f] = reinterpret_cast<const f32x4 *>(g.k)[at];
+      qr[f] = reinterpret_cast<const f32x4 *>(g.q)[at];
+      vr[f] = reinterpret_cast<const f32x4 *>(g.v)[at];
+    }
+    if (tid < GDN_CHUNK) {
+      const int64_t at = (int64_t)(sq.row0 + min(t0 + tid, sq.len - 1)) * H + h;
+      ar = g.alpha[at];
+      br = g.beta[at];
+    }
+  };
   float cs = 1.0f;  // the state is cs s
+  if (sq.len > 0) fetch(0);
   for (int t0 = 0; t0 < sq.len; t0 += GDN_CHUNK) {
     const int nt = min(GDN_CHUNK, sq.len - t0);
     __syncthreads();
-    for (int e = i; e < nt * (GDN_D / 4); e += 128) {
-      const int tt = e / (GDN_D / 4), c = e % (GDN_D / 4);
-      const int64_t row = sq.row0 + t0 + tt;
-      ks[tt][c] = reinterpret_cast<const float4 *>(g.k + (row * H + h) * GDN_D)[c];
-      qs[tt][c] = reinterpret_cast<const float4 *>(g.q + (row * H + h) * GDN_D)[c];
+#pragma unroll
+    for (int f = 0; f < PF; ++f) {
+      const int e = f * NT + tid, tt = e / C4, x = e % C4;
+      ks[tt][x] = kr[f];
+      qs[tt][x] = qr[f];
+      vs[tt][x] = vr[f];
     }
-    if (i < nt) {
-      const int64_t row = sq.row0 + t0 + i;
-      al[i] = g.alpha[row * H + h];
-      be[i] = g.beta[row * H + h];
+    if (tid < GDN_CHUNK) {
+      al[tid] = ar;
+      be[tid] = br;
     }
     __syncthreads();
+    if (t0 + GDN_CHUNK < sq.len) fetch(t0 + GDN_CHUNK);
     for (int tt = 0; tt < nt; ++tt) {
-      const int64_t row = sq.row0 + t0 + tt;
       const float a = al[tt], b = be[tt];
-      const float vv = g.v[(row * H + h) * GDN_D + i];
-      const float4 k0 = ks[tt][2 * ln], k1 = ks[tt][2 * ln + 1];
-      const float4 q0 = qs[tt][2 * ln], q1 = qs[tt][2 * ln + 1];
-      const float kk[8] = {k0.x, k0.y, k0.z, k0.w, k1.x, k1.y, k1.z, k1.w};
-      const float qq[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
+      const float *kp = reinterpret_cast<const float *>(ks[tt]) + 8 * n + c;
+      const float *qp = reinterpret_cast<const float *>(qs[tt]) + 8 * n + c;
+      const float vv = reinterpret_cast<const float *>(vs[tt])[i];
+      const float kk[2] = {kp[0], kp[4]}, qq[2] = {qp[0], qp[4]};
       cs *= a;
       if (cs < 0x1p-40f) {  // uniform: fold c into X
 #pragma unroll
-        for (int c = 0; c < GDN_D; ++c) s[c] *= cs;
+        for (int m = 0; m < GDN_PART; ++m) s[m] *= cs;
         cs = 1.0f;
       }
-      float p[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-      gdn_dot(s, kk, p, std::make_integer_sequence<int, GDN_D>{});
-      const float pred = cs * ((p[0] + p[1]) + (p[2] + p[3]));
+      float p = 0.0f;
+      gdn_dot(s, kk, p, std::make_integer_sequence<int, GDN_PART / 8>{});
+      const float pred = cs * gdn_row_sum(p);
       const float e = b * (vv - pred) / cs;
-      float o[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-      gdn_update_dot(s, kk, qq, e, o, std::make_integer_sequence<int, GDN_D>{});
-      g.o[(row * H + h) * GDN_D + i] = cs * ((o[0] + o[1]) + (o[2] + o[3]));
+      float o = 0.0f;
+      gdn_update_dot(s, kk, qq, e, o, std::make_integer_sequence<int, GDN_PART / 4>{});
+      o = cs * gdn_row_sum(o);
+      if (c == 0) reinterpret_cast<float *>(os[tt])[i] = o;
     }
+    __syncthreads();
+    for (int e = tid; e < nt * C4; e += NT)
+      reinterpret_cast<f32x4 *>(g.o)[((int64_t)(sq.row0 + t0 + e / C4) * H + h) * C4 + e % C4] = os[e / C4][e % C4];
   }
-#pragma unroll
-  for (int c = 0; c < GDN_D; ++c) s[c] *= cs;
   if (sq.fin >= 0) {
-    float4 *dst = reinterpret_cast<float4 *>(g.S_fin + (((int64_t)sq.fin * H + h) * GDN_D + i) * GDN_D);
+    __syncthreads();
 #pragma unroll
-    for (int c = 0; c < GDN_D / 4; ++c) dst[c] = make_float4(s[4 * c], s[4 * c + 1], s[4 * c + 2], s[4 * c + 3]);
+    for (int m = 0; m < GDN_PART; ++m) const_cast<float *>(mine)[4 * (m ^ (i & 31))] = s[m] * cs;
+    __syncthreads();
+    f32x4 *dst = reinterpret_cast<f32x4 *>(g.S_fin) + ((int64_t)sq.fin * H + h) * GDN_D * C4;
+#pragma unroll
+    for (int f = 0; f < SP; ++f) {
+      const int e = f * NT + tid, r = e / C4, x = e % C4;
+      dst[e] = sh[r * C4 + (x ^ (r & 31))];
+    }
   }
 }
 
@@ -615,7 +703,7 @@ hipError_t launch_gdn_conv(const GdnConvArgs &g, int R, hipStream_t st) {
 hipError_t launch_gdn_recur(const GdnRecurArgs &g, int nseq, hipStream_t st) {
   if (nseq <= 0) return hipSuccess;
   if (g.dk != GDN_D || g.dv != GDN_D) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(gdn_recur_kernel, dim3(nseq * g.H), dim3(128), 0, st, g);
+  hipLaunchKernelGGL(gdn_recur_kernel, dim3(nseq * g.H), dim3(512), 0, st, g);
   return hipGetLastError();
 }
 

@@ -1157,14 +1157,13 @@ Status prefill(jet_model *m, int32_t n_q, const int64_t *offs, const int32_t *to
         seqs.push_back({(int32_t)base, (int32_t)P, -1, q});
       }
       // prefixes in the 16-bit modes run the chunked form (fp16 operands, or
-      // bf16 pairs in the pair mode), longest first (no round of the launch
-      // waits on one long sequence); models with routed experts keep the fp32
+      // bf16 pairs in the pair mode); models with routed experts keep the fp32
       // stepwise recurrence: a top-k routing decision turns its rounding into
-      // a different expert for rows near a tie
+      // a different expert for rows near a tie. Longest first: no round of the
+      // launch waits on one long sequence.
       gp.chunked = m->kdt != 1 && !h.n_experts;
-      if (gp.chunked)
-        std::stable_sort(seqs.begin(), seqs.end(),
-                         [](const jetk::GdnSeq &a, const jetk::GdnSeq &b) { return a.len > b.len; });
+      std::stable_sort(seqs.begin(), seqs.end(),
+                       [](const jetk::GdnSeq &a, const jetk::GdnSeq &b) { return a.len > b.len; });
       TRY(upload(m, "pre_ghist", hist, &gp.hist));
       TRY(upload(m, "pre_gtslot", tslot, &gp.tail_slot));
       TRY(upload(m, "pre_gseqs", seqs, &gp.seqs));
