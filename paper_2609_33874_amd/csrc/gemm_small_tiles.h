@@ -48,6 +48,8 @@ struct TileTypes {
   }
 };
 
+// (the grouped GEMMs of launch_gemm_grouped name c1 and c3 of SmallPlain and c0
+// and c1 of SmallSwiglu)
 template <typename T>
 struct SmallPlain<T, 1, 0> {
   using c0 = SCfg<T, 1, 0, 1, 1, 2, 1, 6>;      // 32 x 16

@@ -250,12 +250,14 @@ hipError_t launch_moe_scatter(const void *x, int64_t row_bytes, int R, int top_k
 // null); y in the compute type of dtype.
 hipError_t launch_moe_combine(int dtype, const void *y, const int *slot_of, const float *wts, int top_k,
                               const float *ys, const float *gate, int R, int d, float *resid, hipStream_t st);
-// Grouped GEMM: row tile t of A (tiles of gemm_group_rows(dtype, big) rows) is
+// Grouped GEMM: row tile t of A (tiles of bm rows, bm from gemm_group_rows) is
 // multiplied by B + tile_group[t] * group_stride (elements); tiles with
 // tile_group -1 are skipped. Otherwise as launch_gemm (no pair operands).
-// big (fp16 only): 256-row tiles, for segments of many rows.
-int gemm_group_rows(int dtype, int big);
-hipError_t launch_gemm_grouped(int dtype, int big, int epi, const void *A, int64_t lda, const void *B, int64_t ldb,
+// gemm_group_rows: tile rows for segments of avg rows on average, gate/up
+// over d columns and down over F; gemm_group_rows_max: the most it returns.
+int gemm_group_rows(int dtype, double avg, int d, int F);
+int gemm_group_rows_max(int dtype);
+hipError_t launch_gemm_grouped(int dtype, int bm, int epi, const void *A, int64_t lda, const void *B, int64_t ldb,
                                int64_t group_stride, const int *tile_group, int M, int N, int K, void *out,
                                int64_t ldo, float oscale, hipStream_t st);
 

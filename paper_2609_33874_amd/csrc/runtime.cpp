@@ -835,10 +835,7 @@ Status moe_ffn(jet_model *m, const Layer &ly, const WaveBufs &b, int64_t R) {
   const ModelHeader &h = m->h;
   const int E = (int)h.n_experts, k = (int)h.top_k;
   const int64_t Fe = h.moe_ffn, Fs = h.shared_ffn, d = h.d;
-  // 256-row tiles when the segments average 1024 rows or more (padding costs
-  // at most an eighth), else 128
-  const int big = m->kdt == 2 && R * k >= 1024 * (int64_t)E;
-  const int bm = jetk::gemm_group_rows(m->kdt, big);
+  const int bm = jetk::gemm_group_rows(m->kdt, (double)(R * k) / E, (int)d, (int)Fe);
   const int64_t S = (R * k + (int64_t)E * (bm - 1) + bm - 1) / bm * bm;  // rows of all segments, at most
   float *logits, *wts, *sg = nullptr, *ys = nullptr;
   int *sel, *tiles, *slot, *chist, *cbase;
@@ -872,14 +869,14 @@ Status moe_ffn(jet_model *m, const Layer &ly, const WaveBufs &b, int64_t R) {
     const double rows = (double)(R * k);
     KTimer t(m, JET_K_GEMM_GATEUP, 2.0 * rows * (double)(2 * Fe) * (double)d,
              (rows * (double)d + rows * (double)Fe) * (double)m->esz);
-    LAUNCH(jetk::launch_gemm_grouped(m->kdt, big, jetk::EPI_SWIGLU, xp, d, ly.w_egu, d, 2 * Fe * d, tiles, (int)S,
+    LAUNCH(jetk::launch_gemm_grouped(m->kdt, bm, jetk::EPI_SWIGLU, xp, d, ly.w_egu, d, 2 * Fe * d, tiles, (int)S,
                                      (int)(2 * Fe), (int)d, hp, Fe, ly.is_egu, m->st));
   }
   {
     const double rows = (double)(R * k);
     KTimer t(m, JET_K_GEMM_DOWN, 2.0 * rows * (double)d * (double)Fe,
              rows * (double)Fe * (double)m->esz + rows * (double)d * (double)m->esz);
-    LAUNCH(jetk::launch_gemm_grouped(m->kdt, big, jetk::EPI_STORE_T, hp, Fe, ly.w_edown, Fe, d * Fe, tiles, (int)S,
+    LAUNCH(jetk::launch_gemm_grouped(m->kdt, bm, jetk::EPI_STORE_T, hp, Fe, ly.w_edown, Fe, d * Fe, tiles, (int)S,
                                      (int)d, (int)Fe, y, d, ly.is_edown, m->st));
   }
   if (Fs) {
@@ -1481,10 +1478,10 @@ void wave_bytes_bound(const jet_model *m, double *per_row, double *fixed) {
   }
   if (h.n_experts) {
     const double k = (double)h.top_k, E = (double)h.n_experts, Fe = (double)h.moe_ffn, Fs = (double)h.shared_ffn;
-    const double bm = (double)std::max(jetk::gemm_group_rows(m->kdt, 0), jetk::gemm_group_rows(m->kdt, 1));
+    const double bm = (double)jetk::gemm_group_rows_max(m->kdt), bm_min = 16.0;
     int64_t n_router = 0;
     for (const Layer &ly : m->layers) n_router = std::max(n_router, ly.n_router);
-    r += (double)n_router * 4 + 3 * k * 4 + (k / bm) * 4 + 2 * E * 4 * k / jetk::kMoeChunk;
+    r += (double)n_router * 4 + 3 * k * 4 + (k / bm_min) * 4 + 2 * E * 4 * k / jetk::kMoeChunk;
     r += k * (2 * d + Fe) * esz;          // routed rows: gathered input, hidden, output
     r += 4 + Fs * esz + d * 4;            // shared expert
     f += (E * bm + bm) * (2 * d + Fe) * esz + 4 * (E + 2) + 2 * E * 4;
