@@ -23,12 +23,13 @@ namespace jetk {
 // Convolution, gates and normalisation of the delta-rule inputs. x:
 // projection output [R][ldx] = q~ | k~ | v~ | z | b | a. One half-wave (32
 // lanes, 4 channels each) takes one group of 128 channels (one head of q~, k~
-// or v~; dk = dv = 128) over a block of GDN_CONV_RB consecutive rows, walked in
-// order: the inputs of the previous three rows stay in registers and are
+// or v~; dk = dv = 128) over a block of RB consecutive rows, walked in order:
+// the inputs of the previous three rows stay in registers and are
 // reused whenever a row's history names the row before it (a row of the same
 // sequence), so every input element is read once. The l2 norm of a q / k head
-// is a reduction over the 32 lanes of the half-wave.
-constexpr int GDN_CONV_RB = 16;
+// is a reduction over the 32 lanes of the half-wave. RB = 16 reads each row
+// little more than once; a call of few rows, whose time is the walk of one
+// block, takes RB = 4.
 
 __device__ __forceinline__ float4 ld4f(const float *p, bool aligned) {
   if (aligned) return *reinterpret_cast<const float4 *>(p);
@@ -37,12 +38,13 @@ __device__ __forceinline__ float4 ld4f(const float *p, bool aligned) {
 
 __device__ __forceinline__ float silu_f(float x) { return x / (1.0f + __expf(-x)); }
 
+template <int RB>
 __global__ __launch_bounds__(256) void gdn_conv_kernel(GdnConvArgs g, int R) {
   const int H = g.H, dk = g.dk, dv = g.dv;
   const int C = 2 * H * dk + H * dv;
   const int ngroups = C / 128;
   const int hw = blockIdx.x * 8 + (threadIdx.x >> 5), lane = threadIdx.x & 31;
-  const int nrb = (R + GDN_CONV_RB - 1) / GDN_CONV_RB;
+  const int nrb = (R + RB - 1) / RB;
   if (hw >= nrb * ngroups) return;  // no barriers or LDS below
   const int rb = hw / ngroups, cg = hw % ngroups;
   const int c = cg * 128 + lane * 4;
@@ -51,7 +53,7 @@ __global__ __launch_bounds__(256) void gdn_conv_kernel(GdnConvArgs g, int R) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) w[e] = *reinterpret_cast<const float4 *>(g.conv_w + (int64_t)(c + e) * 4);
   const float qscale = rsqrtf((float)dk);
-  const int r0 = rb * GDN_CONV_RB, r1 = min(R, r0 + GDN_CONV_RB);
+  const int r0 = rb * RB, r1 = min(R, r0 + RB);
   float4 win[3] = {};  // inputs of rows r - 1, r - 2, r - 3
   // row r + 1's input and history are fetched while row r is processed
   float4 xn = ld4f(g.x + (int64_t)r0 * g.ldx + c, al);
@@ -695,8 +697,12 @@ __global__ __launch_bounds__(256) void gdn_out_kernel(const float *__restrict__ 
 hipError_t launch_gdn_conv(const GdnConvArgs &g, int R, hipStream_t st) {
   if (R <= 0) return hipSuccess;
   if (g.dk != 128 || g.dv != 128) return hipErrorInvalidValue;
-  const int64_t groups = (int64_t)((R + GDN_CONV_RB - 1) / GDN_CONV_RB) * (3 * g.H);
-  hipLaunchKernelGGL(gdn_conv_kernel, dim3((unsigned)((groups + 7) / 8)), dim3(256), 0, st, g, R);
+  // four workgroups per CU with 16 rows each fill the device; below, the time
+  // is one block's walk (48 groups of channels: 59 rows 32 us with 16 rows a
+  // block, 11 with 4; 611 rows 34 and 16; 1479 rows 39 and 27)
+  auto blocks = [&](int rb) { return (unsigned)(((int64_t)((R + rb - 1) / rb) * (3 * g.H) + 7) / 8); };
+  if (blocks(16) >= 1024) hipLaunchKernelGGL(gdn_conv_kernel<16>, dim3(blocks(16)), dim3(256), 0, st, g, R);
+  else hipLaunchKernelGGL(gdn_conv_kernel<4>, dim3(blocks(4)), dim3(256), 0, st, g, R);
   return hipGetLastError();
 }
 

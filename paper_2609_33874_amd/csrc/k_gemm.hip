@@ -616,7 +616,7 @@ static hipError_t run_grouped_epi(int epi, const void *A, int64_t lda, const voi
 // (fp16) from 512 rows a segment: at 656 rows (256 experts, d 2048, F 512)
 // gate/up took 1190 us with 128-row tiles and takes 1010, down 755 and 691.
 // 128-row tiles from 64; below, small tiles, where the stream of the experts'
-// weights bounds the launch, as far as K fills their ring of stages (35 rows:
+// weights bounds the launch, as far as K fills their ring of stages (46 rows:
 // gate/up 346 -> 279 us with 64-row tiles, down 197 -> 208; 16-row tiles up to
 // 12 rows a segment).
 int gemm_group_rows(int dtype, double avg, int d, int F) {
