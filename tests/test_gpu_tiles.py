@@ -27,7 +27,7 @@ CASES = {
     "hybrid_pair": (dict(DENSE, arch="hybrid", n_layers=4, dtype="bf16", d_model=640, ffn=832, gdn_heads=5,
                          gdn_dk=128, gdn_dv=128, conv_kernel=4), J.JET_BF16),
     # the stepwise recurrence over prefixes (chunks of 32 steps)
-    "hybrid_fp32": (dict(DENSE, arch="hybrid", n_layers=4, dtype="fp32", d_model=256, ffn=320, gdn_heads=2,
+    "hybrid_fp32": (dict(DENSE, arch="hybrid", n_layers=4, dtype="f32", d_model=256, ffn=320, gdn_heads=2,
                          gdn_dk=128, gdn_dv=128, conv_kernel=4), J.JET_FP32),
     # routed experts: segments of a few rows, of tens and of hundreds (the
     # oracle is left out: a rounding difference may swap experts of equal logit)
