@@ -25,6 +25,7 @@
 //           tile, the B tile as [K chunk][row] 16-byte units and the tile's
 //           scales, and each B fragment is turned into fp16 q * scale in
 //           registers (exact) before its MFMAs.
+//   LOAD 11 four waves of 128 x 128 with 128-byte rows, see wide_tile.
 // Rows beyond M / N load a clamped valid row; their outputs are discarded.
 #pragma once
 
@@ -50,6 +51,7 @@ struct GCfg {
   static constexpr int BK = CPR * EPC;              // elements per K step
   // LOAD 7 (pair-aware): A holds (hi, lo) planes and both are staged, B once
   static constexpr bool PAIRA = LOAD == 7;
+  static constexpr bool WIDE = LOAD == 11;  // one wave per SIMD
   static constexpr bool INTERLEAVED = LOAD == 7 || LOAD == 8;  // the LOAD 7 / 8 schedule
   // block-quantized B with per-block scales: int8 (LOAD 9) or int4 (LOAD 10)
   static constexpr int QBITS = LOAD == 9 ? 8 : LOAD == 10 ? 4 : 0;
@@ -61,19 +63,21 @@ struct GCfg {
   // each) or, for int4 tiles of 32 per wave, one load with half the lanes
   static constexpr int B_PT = Q8B ? (B_CH * BN >= NT ? B_CH * BN / NT : 1) : BN * CPR / NT;
   static constexpr int BUF = Q8B ? BM * CPR + B_CH * BN + BN / 8 : (BROW0 + BN) * CPR;  // chunks per LDS stage
-  static constexpr size_t LDS_BYTES = sizeof(uint4) * NSTAGE * BUF;
+  static constexpr size_t LDS_BYTES = WIDE ? (size_t)5 * BM * 128 : sizeof(uint4) * NSTAGE * BUF;
   static constexpr int RPI = 64 / CPR;  // tile rows per direct-load wave instruction
   static_assert(BM * CPR % NT == 0 && BN * CPR % NT == 0, "tile/thread mismatch");
   static_assert(BM % (RPI * NWAVES) == 0 && BN % (RPI * NWAVES) == 0, "direct loads fill whole row groups");
   static_assert(BK % 16 == 0, "K step must hold whole MFMA steps");
-  static_assert(LOAD == 0 || LOAD == 2 || LOAD == 4 || LOAD == 7 || LOAD == 8 || LOAD == 9 || LOAD == 10,
+  static_assert(LOAD == 0 || LOAD == 2 || LOAD == 4 || LOAD == 7 || LOAD == 8 || LOAD == 9 || LOAD == 10 ||
+                    WIDE,
                 "tile load schedule");
   static_assert(!Q8B || (BK == 32 && (B_CH * BN % (64 * NWAVES) == 0 || B_CH * BN == 32 * NWAVES) &&
                          BN / 8 == 4 * NWAVES && WN <= 128 && 128 % WN == 0),
                 "quantized B: one quantization block per K step, whole direct-load rounds, 4 scale chunks per wave");
+  static_assert(!WIDE || (BK == 64 && BM == BN && NWAVES == 4), "four waves, buffers of BM 128-byte rows");
   static_assert(INTERLEAVED || Q8B ? NSTAGE >= 2 : LOAD >= 4 ? NSTAGE >= 2 : LOAD == 2 ? NSTAGE >= 3 : NSTAGE == 2,
                 "pipeline depth");
-  static_assert(LOAD < 4 || (BK / 16) % 2 == 0, "fragment pipelining alternates two register sets");
+  static_assert(LOAD < 4 || WIDE || (BK / 16) % 2 == 0, "fragment pipelining alternates two register sets");
 };
 
 // SWZ 0: c ^ (r mod CPR). SWZ 1 (CPR 8): c ^ ((r >> 1) & 7). SWZ 2 (CPR 4):
@@ -500,6 +504,162 @@ __device__ __forceinline__ void tile_issue_direct(const typename C::type *__rest
   }
 }
 
+// ---------------------------------------------------------------------------
+// one wave per SIMD (LOAD 11)
+// ---------------------------------------------------------------------------
+
+template <class F, int... I>
+__device__ __forceinline__ void static_for_seq(F &f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+// f(0), f(1), .., f(N - 1) with compile-time arguments.
+template <int N, class F>
+__device__ __forceinline__ void static_for(F f) {
+  static_for_seq(f, std::make_integer_sequence<int, N>{});
+}
+
+// A wave's fragments of 32 columns.
+template <class C>
+struct WideFrags {
+  static constexpr int NPL = 1;
+  Frag<typename C::type> a[2][NPL][C::MI], b[2][C::NI];
+};
+
+// Waits until the wave's LDS reads are done and at most N direct loads are in
+// flight, and ties the fragments to that wait.
+template <int N, class C>
+__device__ __forceinline__ void wide_wait(WideFrags<C> &f) {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+#pragma unroll
+  for (int k2 = 0; k2 < 2; ++k2) {
+#pragma unroll
+    for (int p = 0; p < WideFrags<C>::NPL; ++p)
+#pragma unroll
+      for (int i = 0; i < C::MI; ++i) asm volatile("" : "+v"(f.a[k2][p][i].v));
+#pragma unroll
+    for (int j = 0; j < C::NI; ++j) asm volatile("" : "+v"(f.b[k2][j].v));
+  }
+}
+
+// One direct load of 16 bytes a lane from p (the same in all lanes) + off. p
+// stays in scalar registers: as a per-lane address, 64 bits a load, it costs
+// the registers of a fragment set.
+__device__ __forceinline__ void wide_load(const char *p, uint32_t off, uint4 *dst) {
+  asm("" : "+s"(p));
+  __builtin_amdgcn_global_load_lds((const void *)(p + off), (lds_void *)dst, 16, 0, 0);
+}
+
+// Four waves of 128 x 128 on a 256 x 256 tile: per product, a wave reads two
+// thirds of the LDS bytes that waves of 64 x 128 read, and the direct loads
+// write through the same LDS ports. A load fetches 128 bytes of a row (a whole
+// cache line: with 64-byte rows every line went from L2 to the CU twice).
+// One wave per SIMD hides nothing behind another wave, so the schedule is laid
+// out by hand: a K step of 64 columns is two runs of MFMAs, each with the LDS
+// reads of the next run's fragments and half of the direct loads between them,
+// the reads over the first three quarters so that the wait at its end finds
+// them done. LDS: three buffers of A and two of B (32 KB each). The barrier in
+// the middle of step s certifies that every wave has step s in registers and
+// that step s + 1 has landed; A of step s + 2 is loaded in the first half of
+// step s, B in the second.
+// Needs KB a multiple of 64, at least 128. Ends with a barrier.
+template <class C>
+__device__ __forceinline__ void wide_tile(const typename C::type *__restrict__ A, int64_t lda,
+                                          const typename C::type *__restrict__ B, int64_t ldb, int M, int N, int KB,
+                                          int m0, int n0, uint4 *lds, f32x16 (&acc)[C::MI][C::NI]) {
+  using T = typename C::type;
+  constexpr int PT = C::A_PT, SLOT = C::BM * C::CPR;  // loads per buffer; chunks of a buffer
+  constexpr int NR = 2 * (C::MI + C::NI), NM = 2 * C::MI * C::NI;  // LDS reads, MFMAs of half a K step
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
+  // Direct loads: byte offsets from the tile's first row (rows past M / N read
+  // the last valid one).
+  const char *pa = (const char *)(A + (int64_t)m0 * lda), *pb = (const char *)(B + (int64_t)n0 * ldb);
+  uint32_t oa[PT], ob[PT];
+#pragma unroll
+  for (int i = 0; i < PT; ++i) {
+    const int r = (i * C::NWAVES + wave) * C::RPI + lane / C::CPR, c = (lane % C::CPR) ^ lds_swz<C>(r);
+    oa[i] = (uint32_t)min(r, M - 1 - m0) * (uint32_t)(lda * sizeof(T)) + (uint32_t)c * 16u;
+    ob[i] = (uint32_t)min(r, N - 1 - n0) * (uint32_t)(ldb * sizeof(T)) + (uint32_t)c * 16u;
+  }
+  auto load = [&](const char *p, uint32_t off, int i, int s, int slot) {
+    wide_load(p + (int64_t)s * 128, off, lds + slot * SLOT + (i * C::NWAVES + wave) * 64);
+  };
+  // LDS addresses of the first fragment of each MFMA step in buffer 0
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void *)lds;
+  uint32_t fa[4], fb[4];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    const int c = kk * 2 + (lane >> 5), ra = wm * C::WM + (lane & 31), rb = wn * C::WN + (lane & 31);
+    fa[kk] = lds0 + (uint32_t)(ra * C::CPR + (c ^ lds_swz<C>(ra))) * 16u;
+    fb[kk] = lds0 + (uint32_t)(rb * C::CPR + (c ^ lds_swz<C>(rb))) * 16u;
+  }
+  // read r of the fragments of half h, from buffers at byte offsets ao, bo
+  auto read = [&](auto r_, auto h_, WideFrags<C> &f, uint32_t ao, uint32_t bo) {
+    constexpr int r = decltype(r_)::value, k2 = r / (NR / 2), q = r % (NR / 2), kk = decltype(h_)::value * 2 + k2;
+    if constexpr (q < C::MI) ds_read16<q * 32 * C::CPR * 16>(f.a[k2][0][q].v, fa[kk] + ao);
+    else ds_read16<(q - C::MI) * 32 * C::CPR * 16>(f.b[k2][q - C::MI].v, fb[kk] + bo);
+  };
+  constexpr uint32_t SB = SLOT * 16;
+  constexpr std::integral_constant<int, 0> h0{};
+  constexpr std::integral_constant<int, 1> h1{};
+  constexpr std::integral_constant<bool, true> yes{};
+  constexpr std::integral_constant<bool, false> no{};
+  // MFMAs of half a step on `cur`; reads of half h into `nxt`; loads of step
+  // s + 2 (LP: MFMAs per load, so that B's, which have less time, go early)
+  auto run = [&](const WideFrags<C> &cur, WideFrags<C> &nxt, auto h, auto reads, uint32_t ao, uint32_t bo, auto loads,
+                 auto lp, const char *p, const uint32_t *off, int s, int slot) {
+    constexpr int LP = decltype(lp)::value;
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<NM>([&](auto m_) {
+      constexpr int m = decltype(m_)::value, k2 = m / (NM / 2), i = m / C::NI % C::MI, j = m % C::NI;
+      tile_mma<C>(acc[i][j], cur.a[k2][0][i], cur.b[k2][j]);
+      if constexpr (decltype(reads)::value) {
+        constexpr int r0 = NR * m * 4 / (NM * 3), r1 = NR * (m + 1) * 4 / (NM * 3);
+        if constexpr (r0 < NR && r1 > r0) read(std::integral_constant<int, r0>{}, h, nxt, ao, bo);
+      }
+      if constexpr (decltype(loads)::value) {
+        if constexpr (m % LP == LP - 1 && m / LP < PT) load(p, off[m / LP], m / LP, s, slot);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  const int nk = KB / C::BK;
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+#pragma unroll
+    for (int i = 0; i < PT; ++i) load(pa, oa[i], i, s, s);
+#pragma unroll
+    for (int i = 0; i < PT; ++i) load(pb, ob[i], i, s, 3 + s);
+  }
+  WideFrags<C> f0, f1;
+  wait_vmcnt<2 * PT>();
+  __builtin_amdgcn_s_barrier();
+  static_for<NR>([&](auto r) { read(r, h0, f0, 0u, 3 * SB); });
+  wide_wait<2 * PT>(f0);
+  int a0 = 0, b0 = 3;  // buffers of step s
+  for (int s = 0; s < nk - 2; ++s) {
+    const int a1 = a0 == 2 ? 0 : a0 + 1, a2 = a1 == 2 ? 0 : a1 + 1, b1 = 7 - b0;
+    run(f0, f1, h1, yes, (uint32_t)a0 * SB, (uint32_t)b0 * SB, yes, std::integral_constant<int, 4>{}, pa, oa, s + 2, a2);
+    wide_wait<PT>(f1);  // all but A of step s + 2
+    __builtin_amdgcn_s_barrier();
+    run(f1, f0, h0, yes, (uint32_t)a1 * SB, (uint32_t)b1 * SB, yes, std::integral_constant<int, 2>{}, pb, ob, s + 2, b0);
+    wide_wait<2 * PT>(f0);
+    a0 = a1;
+    b0 = b1;
+  }
+  const int a1 = a0 == 2 ? 0 : a0 + 1, b1 = 7 - b0;
+  constexpr std::integral_constant<int, NM> never{};
+  run(f0, f1, h1, yes, (uint32_t)a0 * SB, (uint32_t)b0 * SB, no, never, pa, oa, 0, 0);
+  wide_wait<0>(f1);
+  __builtin_amdgcn_s_barrier();
+  run(f1, f0, h0, yes, (uint32_t)a1 * SB, (uint32_t)b1 * SB, no, never, pa, oa, 0, 0);
+  wide_wait<0>(f0);
+  run(f0, f1, h1, yes, (uint32_t)a1 * SB, (uint32_t)b1 * SB, no, never, pa, oa, 0, 0);
+  wide_wait<0>(f1);
+  run(f1, f0, h0, no, 0u, 0u, no, never, pa, oa, 0, 0);
+  __builtin_amdgcn_s_barrier();
+}
+
 // acc = sum over k < K of A[m0 + r][k mod KA] * B[n0 + c][k mod KB]: a plain
 // GEMM when K = KA = KB; with K = 2 KB and KA = K the A rows hold a (hi, lo)
 // bf16 pair of each activation, [a_hi | a_lo], and B is read twice, so the
@@ -685,6 +845,8 @@ __device__ __forceinline__ void gemm_tile(const typename C::type *__restrict__ A
       wait_frags<0>(fa[1], fb[1]);
     }
     __builtin_amdgcn_s_barrier();
+  } else if constexpr (C::WIDE) {
+    wide_tile<C>(A, lda, B, ldb, M, N, KB, m0, n0, lds, acc);
   } else if constexpr (C::Q8B) {
     // The LOAD 8 schedule (see above) with an int8 B operand: B is int8
     // [N][KB] (ldb bytes per row) with fp16 scales Bs; a stage's scales are

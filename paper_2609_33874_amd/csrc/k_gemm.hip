@@ -3,9 +3,9 @@
 // needs fused in (fp32 store, residual add, SwiGLU), and the LM head with a
 // full-vocabulary online log-sum-exp epilogue that never writes logits.
 //
-// Large problems use 256x256 tiles (8 waves, MFMA fragments read one step
-// ahead; in the pair mode the hi and lo planes of A share each B tile) fed by
-// direct global->LDS loads, one barrier per K step. Problems of few tiles
+// Large problems use 256x256 tiles (MFMA fragments read one step ahead; in the
+// pair mode the hi and lo planes of A share each B tile) fed by direct
+// global->LDS loads, one barrier per K step. Problems of few tiles
 // take the smaller tiles of gemm_small.h; which one is chosen by the estimated
 // time of its rounds of workgroups (small_tile_for). Tiles are ordered so that
 // each XCD works on a contiguous band (see tile_coords).
@@ -51,39 +51,60 @@ __device__ __forceinline__ bool staged_epilogue(const GemmArgs<typename C::type>
     } else {
       if ((g.ldo & 3) || (g.N & 3)) return false;
       float *wl = reinterpret_cast<float *>(lds) + wave * 16 * LDF;
+      constexpr int JH = C::WN / SC, NSLAB = 2 * C::MI * JH;
+      // residual rows are loaded DEEP slabs ahead where one wave per SIMD has
+      // the registers (and no other wave to hide the latency)
+      constexpr int DEEP = EPI == 1 && C::WIDE ? 4 : 1;
+      float4 x[DEEP][CH];
+      // row (hr: rows 16 hr .. 16 hr + 15 of the 32-row block) and column of chunk t of slab n
+      auto at = [&](int n, int t, int *row, int *col) {
+        const int q = t * 64 + lane, i = n / (2 * JH), hr = n / JH % 2, jh = n % JH;
+        *row = m0 + wm * C::WM + i * 32 + 16 * hr + q / (SC / 4);
+        *col = n0 + wn * C::WN + jh * SC + 4 * (q % (SC / 4));
+        return *row < g.M && *col < g.N;
+      };
+      auto fetch = [&](int n, float4 (&v)[CH]) {
 #pragma unroll
-      for (int i = 0; i < C::MI; ++i)
+        for (int t = 0; t < CH; ++t) {
+          int row, col;
+          if (at(n, t, &row, &col)) v[t] = *reinterpret_cast<const float4 *>((const float *)g.out + (int64_t)row * g.ldo + col);
+        }
+      };
+      if constexpr (DEEP > 1) {
 #pragma unroll
-        for (int hr = 0; hr < 2; ++hr)  // rows 16 hr .. 16 hr + 15 of the 32-row block
+        for (int n = 0; n < DEEP; ++n) fetch(n, x[n]);
+      }
+      static_for<NSLAB>([&](auto n_) {
+        constexpr int n = decltype(n_)::value, i = n / (2 * JH), hr = n / JH % 2, jh = n % JH;
 #pragma unroll
-          for (int jh = 0; jh < C::WN / SC; ++jh) {
+        for (int jj = 0; jj < SC / 32; ++jj)
 #pragma unroll
-            for (int jj = 0; jj < SC / 32; ++jj)
-#pragma unroll
-              for (int e = 8 * hr; e < 8 * hr + 8; ++e) {
-                const int r = 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3) - 16 * hr;
-                wl[r * LDF + jj * 32 + (lane & 31)] = acc[i][jh * (SC / 32) + jj][e] * g.oscale;
-              }
-            wave_lds_sync();
-#pragma unroll
-            for (int t = 0; t < CH; ++t) {
-              const int q = t * 64 + lane, r = q / (SC / 4), c4 = q % (SC / 4);
-              const int row = m0 + wm * C::WM + i * 32 + 16 * hr + r;
-              const int col = n0 + wn * C::WN + jh * SC + 4 * c4;
-              if (row < g.M && col < g.N) {
-                const float4 v = *reinterpret_cast<const float4 *>(wl + r * LDF + 4 * c4);
-                float4 *o = reinterpret_cast<float4 *>((float *)g.out + (int64_t)row * g.ldo + col);
-                if constexpr (EPI == 0) {
-                  *o = v;
-                } else {
-                  float4 x = *o;
-                  x.x += v.x; x.y += v.y; x.z += v.z; x.w += v.w;
-                  *o = x;
-                }
-              }
-            }
-            wave_lds_sync();
+          for (int e = 8 * hr; e < 8 * hr + 8; ++e) {
+            const int r = 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3) - 16 * hr;
+            wl[r * LDF + jj * 32 + (lane & 31)] = acc[i][jh * (SC / 32) + jj][e] * g.oscale;
           }
+        wave_lds_sync();
+#pragma unroll
+        for (int t = 0; t < CH; ++t) {
+          int row, col;
+          if (at(n, t, &row, &col)) {
+            const int q = t * 64 + lane;
+            const float4 v = *reinterpret_cast<const float4 *>(wl + q / (SC / 4) * LDF + 4 * (q % (SC / 4)));
+            float4 *o = reinterpret_cast<float4 *>((float *)g.out + (int64_t)row * g.ldo + col);
+            if constexpr (EPI == 0) {
+              *o = v;
+            } else {
+              float4 y;
+              if constexpr (DEEP > 1) y = x[n % DEEP][t];
+              else y = *o;
+              y.x += v.x; y.y += v.y; y.z += v.z; y.w += v.w;
+              *o = y;
+            }
+          }
+        }
+        if constexpr (DEEP > 1 && n + DEEP < NSLAB) fetch(n + DEEP, x[n % DEEP]);
+        wave_lds_sync();
+      });
       return true;
     }
   } else if constexpr (EPI == 2 && sizeof(T) == 2) {
@@ -349,25 +370,26 @@ using PairB = GCfg<bf16, 256, 256, 64, 128, 7, 2, 3, 4>;
 using PairS = GCfg<bf16, 128, 128, 32, 64, 7, 2, 3, 4>;
 using SmallB = GCfg<bf16, 256, 128, 64, 64, 2, 1, 3, 8>;
 using CfgF = GCfg<float, 128, 128, 64, 64, 0, 1>;
-// fp16 operands: the LOAD 7 schedule with a single A plane (three 32 KB
-// stages of 32-column A and B tiles), 256x256 tiles with waves of 64 x 128,
-// or 128x128 tiles (the last round of a large launch, grouped GEMMs, and
-// problems of few tiles whose K is too short for gemm_small.h); the LM head on the same
-// 256x256 schedule (16% faster than the two-stage 128-byte-row one).
-using HalfB = GCfg<f16, 256, 256, 64, 128, 8, 2, 3, 4>;
+// fp16 operands: 256x256 tiles of four waves (wide_tile). Against eight waves
+// of 64 x 128 over 64-byte rows (LOAD 8), 67007 rows, ms: gate/up 17920 x 1536
+// 3.50 -> 3.39, down 1536 x 8960 2.01 -> 1.73, QKV 2048 x 1536 0.53 -> 0.47;
+// output projection 1536 x 1536 0.49 (256x128 tiles, two workgroups per CU)
+// -> 0.46. Without the direct loads the down projection takes 1.57, without
+// the fragment reads too 1.43 (a power-limited MFMA rate).
+using HalfB = GCfg<f16, 256, 256, 128, 128, 11, 1, 2, 8>;
+// ... and 128x128 tiles on the LOAD 8 schedule (the last round of a large
+// launch, grouped GEMMs, and problems whose K is too short for the others).
 using HalfS = GCfg<f16, 128, 128, 32, 64, 8, 2, 3, 4>;
-// Residual-add GEMMs with a short K loop (the attention output projection):
-// 256x128 tiles, two workgroups per CU, so one tile's fp32 read-modify-write
-// epilogue overlaps another's K loop (measured 16% faster than 256x256 at
-// 134k x 1536 x 1536).
-using HalfM = GCfg<f16, 256, 128, 64, 64, 8, 2, 3, 4>;
+// K loops that HalfB runs.
+static bool half_big_k(int K) { return K % 64 == 0 && K >= 128; }
 // (hi, lo) fp16 pair A operands: the bf16 pair schedules with fp16 operands
 using HalfPairB = GCfg<f16, 256, 256, 64, 128, 7, 2, 3, 4>;
 using HalfPairS = GCfg<f16, 128, 128, 32, 64, 7, 2, 3, 4>;
 // LM head: the 256x256 schedules transposed (F rows x 256 vocabulary rows), and
-// 64- and 128-row tiles of the same waves for few rows.
+// 64- and 128-row tiles for few rows.
 template <typename T, bool PAIR>
-using Lm = GCfg<T, 256, 256, 64, 128, PAIR ? 7 : 8, 2, 3, 4, 1>;
+using Lm = std::conditional_t<PAIR, GCfg<T, 256, 256, 64, 128, 7, 2, 3, 4, 1>,
+                              GCfg<T, 256, 256, 128, 128, 11, 1, 2, 8, 1>>;
 template <typename T, bool PAIR>
 using LmMid = GCfg<T, 128, 256, 64, 128, PAIR ? 7 : 8, 2, 3, 4, 1>;
 template <typename T, bool PAIR>
@@ -518,9 +540,8 @@ hipError_t launch_gemm(int dtype, int epi, const void *A, int64_t lda, const voi
     }
     const int c = small_tile_for<f16, 1, 0>(epi, M, N, K, kBigF16);
     if (c >= 0) return small_gemm_f16(epi, c, gemm_args<f16>(A, lda, B, ldb, M, N, K, 0, out, ldo, oscale), st);
-    if (big_tiles < 128) return run_epi<HalfS>(epi, A, lda, B, ldb, M, N, K, 0, out, ldo, oscale, st);
-    if (epi == EPI_RESID_ADD && K <= 2048)
-      return run_gemm_tail<HalfM, 1>(A, lda, B, ldb, M, N, K, out, ldo, oscale, st);
+    if (big_tiles < 128 || !half_big_k(K))
+      return run_epi<HalfS>(epi, A, lda, B, ldb, M, N, K, 0, out, ldo, oscale, st);
     switch (epi) {
       case EPI_STORE_F32: return run_gemm_tail<HalfB, 0>(A, lda, B, ldb, M, N, K, out, ldo, oscale, st);
       case EPI_RESID_ADD: return run_gemm_tail<HalfB, 1>(A, lda, B, ldb, M, N, K, out, ldo, oscale, st);
@@ -622,7 +643,7 @@ static hipError_t run_grouped_epi(int epi, const void *A, int64_t lda, const voi
 int gemm_group_rows(int dtype, double avg, int d, int F) {
   if (dtype == 1) return CfgF::BM;
   if (dtype != 2) return SmallB::BM;
-  if (avg >= 512.0) return HalfB::BM;
+  if (avg >= 512.0 && half_big_k(d) && half_big_k(F)) return HalfB::BM;
   if (avg >= 64.0) return HalfS::BM;
   using S = SmallSwiglu<f16, 1, 0>;
   using P = SmallPlain<f16, 1, 0>;
@@ -679,14 +700,14 @@ static int rope_tile_for(int dtype, int qbits, int pair, int M, int N, int K) {
   if (pair) return small_tile_for<f16, 2, 0>(EPI_QKV_ROPE, M, N, K, kBigPair);
   return small_tile_for<f16, 1, 0>(EPI_QKV_ROPE, M, N, K, kBigF16);
 }
-static bool rope_big_ok(int dtype, int qbits, int pair, int M, int N) {
-  return !qbits && (dtype == 2 || (dtype == 0 && pair)) &&
+static bool rope_big_ok(int dtype, int qbits, int pair, int M, int N, int K) {
+  return !qbits && (pair ? dtype == 0 || dtype == 2 : dtype == 2 && half_big_k(K)) &&
          (int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 128;
 }
 
 bool gemm_qkv_rope_ok(int dtype, int qbits, int pair, int M, int N, int K, int head_dim) {
   if (head_dim != 128 || N % 128 || M <= 0 || dtype == 1) return false;
-  return rope_tile_for(dtype, qbits, pair, M, N, K) >= 0 || rope_big_ok(dtype, qbits, pair, M, N);
+  return rope_tile_for(dtype, qbits, pair, M, N, K) >= 0 || rope_big_ok(dtype, qbits, pair, M, N, K);
 }
 
 hipError_t launch_gemm_qkv_rope(int dtype, int qbits, const void *A, int64_t lda, const void *B, const uint16_t *Bs,
@@ -746,7 +767,7 @@ static hipError_t run_lmhead_rows(const void *W, const void *F, int V, int R, in
                                   hipStream_t st) {
   if (R <= 64)
     return run_lmhead<LmSmall<T, PAIR>>(W, F, V, R, K, tiles_per_split, wscale, part_m, part_s, target, zt, st);
-  if (R <= 128)
+  if (R <= 128 || !half_big_k(K))
     return run_lmhead<LmMid<T, PAIR>>(W, F, V, R, K, tiles_per_split, wscale, part_m, part_s, target, zt, st);
   return run_lmhead<Lm<T, PAIR>>(W, F, V, R, K, tiles_per_split, wscale, part_m, part_s, target, zt, st);
 }
