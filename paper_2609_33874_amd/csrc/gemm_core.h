@@ -25,7 +25,8 @@
 //           tile, the B tile as [K chunk][row] 16-byte units and the tile's
 //           scales, and each B fragment is turned into fp16 q * scale in
 //           registers (exact) before its MFMAs.
-//   LOAD 11 four waves of 128 x 128 with 128-byte rows, see wide_tile.
+//   LOAD 11 four waves of 128 x 128 with 128-byte rows, see wide_tile;
+//   LOAD 12 the same for a pair A operand, see wide_pair_tile.
 // Rows beyond M / N load a clamped valid row; their outputs are discarded.
 #pragma once
 
@@ -50,8 +51,8 @@ struct GCfg {
   static constexpr int EPC = 16 / (int)sizeof(T);  // elements per 16-byte chunk
   static constexpr int BK = CPR * EPC;              // elements per K step
   // LOAD 7 (pair-aware): A holds (hi, lo) planes and both are staged, B once
-  static constexpr bool PAIRA = LOAD == 7;
-  static constexpr bool WIDE = LOAD == 11;  // one wave per SIMD
+  static constexpr bool PAIRA = LOAD == 7 || LOAD == 12;
+  static constexpr bool WIDE = LOAD == 11 || LOAD == 12;  // one wave per SIMD
   static constexpr bool INTERLEAVED = LOAD == 7 || LOAD == 8;  // the LOAD 7 / 8 schedule
   // block-quantized B with per-block scales: int8 (LOAD 9) or int4 (LOAD 10)
   static constexpr int QBITS = LOAD == 9 ? 8 : LOAD == 10 ? 4 : 0;
@@ -74,7 +75,7 @@ struct GCfg {
   static_assert(!Q8B || (BK == 32 && (B_CH * BN % (64 * NWAVES) == 0 || B_CH * BN == 32 * NWAVES) &&
                          BN / 8 == 4 * NWAVES && WN <= 128 && 128 % WN == 0),
                 "quantized B: one quantization block per K step, whole direct-load rounds, 4 scale chunks per wave");
-  static_assert(!WIDE || (BK == 64 && BM == BN && NWAVES == 4), "four waves, buffers of BM 128-byte rows");
+  static_assert(!WIDE || (BK == (PAIRA ? 32 : 64) && BM == BN && NWAVES == 4), "four waves, buffers of BM 128-byte rows");
   static_assert(INTERLEAVED || Q8B ? NSTAGE >= 2 : LOAD >= 4 ? NSTAGE >= 2 : LOAD == 2 ? NSTAGE >= 3 : NSTAGE == 2,
                 "pipeline depth");
   static_assert(LOAD < 4 || WIDE || (BK / 16) % 2 == 0, "fragment pipelining alternates two register sets");
@@ -521,7 +522,7 @@ __device__ __forceinline__ void static_for(F f) {
 // A wave's fragments of 32 columns.
 template <class C>
 struct WideFrags {
-  static constexpr int NPL = 1;
+  static constexpr int NPL = C::PAIRA ? 2 : 1;
   Frag<typename C::type> a[2][NPL][C::MI], b[2][C::NI];
 };
 
@@ -657,6 +658,126 @@ __device__ __forceinline__ void wide_tile(const typename C::type *__restrict__ A
   run(f0, f1, h1, yes, (uint32_t)a1 * SB, (uint32_t)b1 * SB, no, never, pa, oa, 0, 0);
   wide_wait<0>(f1);
   run(f1, f0, h0, no, 0u, 0u, no, never, pa, oa, 0, 0);
+  __builtin_amdgcn_s_barrier();
+}
+
+// wide_tile for a (hi, lo) pair A operand (lo KB columns after hi). The planes
+// of A come in stages of 32 columns (three of 32 KB, hi rows then lo rows), B
+// in two buffers of 64 columns. Half step t runs 2 x 32 MFMAs on its fragments,
+// reads those of t + 1 and loads A of t + 3 into the stage of t; the odd ones
+// load B of the step after next first.
+// Needs KB a multiple of 64, at least 128. Ends with a barrier.
+template <class C>
+__device__ __forceinline__ void wide_pair_tile(const typename C::type *__restrict__ A, int64_t lda,
+                                               const typename C::type *__restrict__ B, int64_t ldb, int M, int N,
+                                               int KB, int m0, int n0, uint4 *lds, f32x16 (&acc)[C::MI][C::NI]) {
+  using T = typename C::type;
+  constexpr int PA = C::A_PT, PB = 2 * C::B_PT, SLOT = C::BM * 8;      // loads of a plane, of B; chunks of a buffer
+  constexpr int NR = 2 * (2 * C::MI + C::NI), NM = 4 * C::MI * C::NI;  // LDS reads, MFMAs of half a step
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
+  auto swz_b = [](int r) { return (r >> 1) & 7; };
+  const char *pa = (const char *)(A + (int64_t)m0 * lda), *pb = (const char *)(B + (int64_t)n0 * ldb);
+  const int64_t lo = (int64_t)KB * sizeof(T);
+  uint32_t oa[PA], ob[PB];
+#pragma unroll
+  for (int i = 0; i < PA; ++i) {
+    const int r = (i * C::NWAVES + wave) * 16 + lane / 4, c = (lane % 4) ^ lds_swz<C>(r);
+    oa[i] = (uint32_t)min(r, M - 1 - m0) * (uint32_t)(lda * sizeof(T)) + (uint32_t)c * 16u;
+  }
+#pragma unroll
+  for (int i = 0; i < PB; ++i) {
+    const int r = (i * C::NWAVES + wave) * 8 + lane / 8, c = (lane % 8) ^ swz_b(r);
+    ob[i] = (uint32_t)min(r, N - 1 - n0) * (uint32_t)(ldb * sizeof(T)) + (uint32_t)c * 16u;
+  }
+  // load l of A of half step t into stage a; load l of B of step s into buffer b
+  auto load_a = [&](int l, int t, int a) {
+    wide_load(pa + (l >= PA ? lo : 0) + (int64_t)t * 64, oa[l % PA],
+              lds + a * SLOT + (l >= PA ? C::BM * 4 : 0) + (l % PA * C::NWAVES + wave) * 64);
+  };
+  auto load_b = [&](int l, int s, int b) {
+    wide_load(pb + (int64_t)s * 128, ob[l], lds + b * SLOT + (l * C::NWAVES + wave) * 64);
+  };
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void *)lds;
+  uint32_t fa[2], fb[4];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    const int c = kk * 2 + (lane >> 5), ra = wm * C::WM + (lane & 31), rb = wn * C::WN + (lane & 31);
+    if (kk < 2) fa[kk] = lds0 + (uint32_t)(ra * 4 + (c ^ lds_swz<C>(ra))) * 16u;
+    fb[kk] = lds0 + (uint32_t)(rb * 8 + (c ^ swz_b(rb))) * 16u;
+  }
+  auto read = [&](auto r_, auto h_, WideFrags<C> &f, uint32_t ao, uint32_t bo) {
+    constexpr int r = decltype(r_)::value, k2 = r / (NR / 2), q = r % (NR / 2), kk = decltype(h_)::value * 2 + k2;
+    if constexpr (q < 2 * C::MI)
+      ds_read16<(q / C::MI * C::BM + q % C::MI * 32) * 64>(f.a[k2][q / C::MI][q % C::MI].v, fa[k2] + ao);
+    else ds_read16<(q - 2 * C::MI) * 32 * 128>(f.b[k2][q - 2 * C::MI].v, fb[kk] + bo);
+  };
+  constexpr uint32_t SB = SLOT * 16;
+  constexpr std::integral_constant<int, 0> h0{};
+  constexpr std::integral_constant<int, 1> h1{};
+  constexpr std::integral_constant<int, 2> ab{};
+  // loads: 0 none, 1 A of half step t into stage a, 2 B of step s into buffer b first
+  auto run = [&](const WideFrags<C> &cur, WideFrags<C> &nxt, auto h, uint32_t ao, uint32_t bo, auto loads, int t,
+                 int a, int s, int b) {
+    constexpr int LD = decltype(loads)::value, LP = LD == 2 ? 3 : 6;
+    constexpr bool READS = decltype(h)::value >= 0;
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<NM>([&](auto m_) {
+      constexpr int m = decltype(m_)::value, k2 = m / (NM / 2), pl = m / (C::MI * C::NI) % 2, i = m / C::NI % C::MI,
+                    j = m % C::NI;
+      tile_mma<C>(acc[i][j], cur.a[k2][pl][i], cur.b[k2][j]);
+      if constexpr (READS) {
+        constexpr int r0 = NR * m * 4 / (NM * 3), r1 = NR * (m + 1) * 4 / (NM * 3);
+        if constexpr (r0 < NR && r1 > r0) read(std::integral_constant<int, r0>{}, h, nxt, ao, bo);
+      }
+      if constexpr (LD > 0 && m % LP == LP - 1) {
+        constexpr int l = m / LP;
+        if constexpr (LD == 2 && l < PB) load_b(l, s, b);
+        else if constexpr (l - (LD == 2 ? PB : 0) < 2 * PA) load_a(l - (LD == 2 ? PB : 0), t, a);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  const int ns = KB / 64;
+  static_for<2>([&](auto s_) {
+    constexpr int s = decltype(s_)::value;
+#pragma unroll
+    for (int l = 0; l < 2 * PA; ++l) load_a(l, s, s);
+#pragma unroll
+    for (int l = 0; l < PB; ++l) load_b(l, s, 3 + s);
+  });
+#pragma unroll
+  for (int l = 0; l < 2 * PA; ++l) load_a(l, 2, 2);
+  WideFrags<C> f0, f1;
+  wait_vmcnt<4 * PA + PB>();
+  __builtin_amdgcn_s_barrier();
+  static_for<NR>([&](auto r) { read(r, h0, f0, 0u, 3 * SB); });
+  wide_wait<2 * PA + PB>(f0);
+  __builtin_amdgcn_s_barrier();
+  int a0 = 0, b0 = 3;  // stage of half step 2 s, buffer of B of step s
+  auto inc = [](int a) { return a == 2 ? 0 : a + 1; };
+  for (int s = 0; s < ns - 2; ++s) {
+    const int a1 = inc(a0), a2 = inc(a1), b1 = 7 - b0;
+    run(f0, f1, h1, (uint32_t)a1 * SB, (uint32_t)b0 * SB, h1, 2 * s + 3, a0, 0, 0);
+    wide_wait<2 * PA>(f1);  // all but A of half step 2 s + 3
+    __builtin_amdgcn_s_barrier();
+    run(f1, f0, h0, (uint32_t)a2 * SB, (uint32_t)b1 * SB, ab, 2 * s + 4, a1, s + 2, b0);
+    wide_wait<2 * PA + PB>(f0);  // A of half step 2 s + 3 has landed
+    __builtin_amdgcn_s_barrier();
+    a0 = a2;
+    b0 = b1;
+  }
+  const int a1 = inc(a0), a2 = inc(a1), b1 = 7 - b0;
+  constexpr std::integral_constant<int, -1> none{};
+  run(f0, f1, h1, (uint32_t)a1 * SB, (uint32_t)b0 * SB, h1, 2 * ns - 1, a0, 0, 0);
+  wide_wait<2 * PA>(f1);
+  __builtin_amdgcn_s_barrier();
+  run(f1, f0, h0, (uint32_t)a2 * SB, (uint32_t)b1 * SB, h0, 0, 0, 0, 0);
+  wide_wait<0>(f0);
+  __builtin_amdgcn_s_barrier();
+  run(f0, f1, h1, (uint32_t)a0 * SB, (uint32_t)b1 * SB, h0, 0, 0, 0, 0);
+  wide_wait<0>(f1);
+  run(f1, f0, none, 0u, 0u, h0, 0, 0, 0, 0);
   __builtin_amdgcn_s_barrier();
 }
 
@@ -846,7 +967,8 @@ __device__ __forceinline__ void gemm_tile(const typename C::type *__restrict__ A
     }
     __builtin_amdgcn_s_barrier();
   } else if constexpr (C::WIDE) {
-    wide_tile<C>(A, lda, B, ldb, M, N, KB, m0, n0, lds, acc);
+    if constexpr (C::PAIRA) wide_pair_tile<C>(A, lda, B, ldb, M, N, KB, m0, n0, lds, acc);
+    else wide_tile<C>(A, lda, B, ldb, M, N, KB, m0, n0, lds, acc);
   } else if constexpr (C::Q8B) {
     // The LOAD 8 schedule (see above) with an int8 B operand: B is int8
     // [N][KB] (ldb bytes per row) with fp16 scales Bs; a stage's scales are

@@ -111,11 +111,11 @@ __device__ __forceinline__ bool staged_epilogue(const GemmArgs<typename C::type>
     constexpr int OC = C::WN / 2, LDH = OC + 8;  // output columns of a wave, padded row (elements)
     constexpr int CH = 32 * OC / 8 / 64;         // 16-byte chunks per lane per 32-row slab
     static_assert(CH >= 1 && (32 * OC / 8) % 64 == 0, "slab of whole chunk rounds");
-    if constexpr ((size_t)C::NWAVES * 32 * LDH * sizeof(T) > C::LDS_BYTES) {
+    if constexpr ((size_t)(C::PAIRA ? 2 : 1) * C::NWAVES * 32 * LDH * sizeof(T) > C::LDS_BYTES) {
       return false;
     } else {
-      if (g.pair_out || (g.ldo & 7)) return false;
-      T *wl = reinterpret_cast<T *>(lds) + wave * 32 * LDH;
+      if ((g.ldo & 7) || (g.pair_out && ((g.N & 15) || !C::PAIRA))) return false;
+      T *wl = reinterpret_cast<T *>(lds) + wave * 32 * LDH, *wl_lo = wl + C::NWAVES * 32 * LDH;
       const int f0 = (n0 + wn * C::WN) >> 1;  // first output column of the wave
 #pragma unroll
       for (int i = 0; i < C::MI; ++i) {
@@ -125,9 +125,14 @@ __device__ __forceinline__ bool staged_epilogue(const GemmArgs<typename C::type>
           for (int e = 0; e < 16; ++e) {
             const float gt = acc[i][2 * jp][e] * g.oscale, up = acc[i][2 * jp + 1][e] * g.oscale;
             // silu(g) = g / (1 + e^-g) with the hardware reciprocal (~1 ulp)
-            const float v = gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * up;
+            float v = gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * up;
+            // the remainder is of the rounded product, as in every other tile
+            // (not a fused multiply-subtract)
+            if constexpr (C::PAIRA) asm("" : "+v"(v));
             const int r = 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-            wl[r * LDH + jp * 32 + (lane & 31)] = from_f<T>(v);
+            const T hi = from_f<T>(v);
+            wl[r * LDH + jp * 32 + (lane & 31)] = hi;
+            if constexpr (C::PAIRA) wl_lo[r * LDH + jp * 32 + (lane & 31)] = from_f<T>(v - to_f<T>(hi));
           }
         wave_lds_sync();
 #pragma unroll
@@ -135,9 +140,13 @@ __device__ __forceinline__ bool staged_epilogue(const GemmArgs<typename C::type>
           const int q = t * 64 + lane, r = q / (OC / 8), c8 = q % (OC / 8);
           const int row = m0 + wm * C::WM + i * 32 + r;
           const int gcol = n0 + wn * C::WN + 64 * (c8 / 4);  // first gate column of the chunk's block
-          if (row < g.M && gcol < g.N)
-            *reinterpret_cast<uint4 *>((T *)g.out + (int64_t)row * g.ldo + f0 + 8 * c8) =
-                *reinterpret_cast<const uint4 *>(wl + r * LDH + 8 * c8);
+          if (row < g.M && gcol < g.N) {
+            T *o = (T *)g.out + (int64_t)row * g.ldo + f0 + 8 * c8;
+            *reinterpret_cast<uint4 *>(o) = *reinterpret_cast<const uint4 *>(wl + r * LDH + 8 * c8);
+            if constexpr (C::PAIRA)
+              if (g.pair_out)
+                *reinterpret_cast<uint4 *>(o + (g.N >> 1)) = *reinterpret_cast<const uint4 *>(wl_lo + r * LDH + 8 * c8);
+          }
         }
         wave_lds_sync();
       }
@@ -360,11 +369,12 @@ __global__ __launch_bounds__(C::NT) void lmhead_lse_kernel(const typename C::typ
 // rows: the 256x256 tiles with fragments read one MFMA step ahead (two stages
 // of 64 KB), the 256x128 tiles with three stages.
 using BigB = GCfg<bf16, 256, 256, 128, 64, 4, 1, 2, 8>;
-// Pair mode: the (hi, lo) planes of A and one B tile per 32-column stage
-// (3 x 16 KB, three stages, two tiles in flight, each tile's loads spread
-// over the first MFMA step of the step before), waves of 64 x 128 so each B
-// fragment serves both planes.
-using PairB = GCfg<bf16, 256, 256, 64, 128, 7, 2, 3, 4>;
+// Pair mode: 256x256 tiles of four waves, the (hi, lo) planes of A against one
+// B tile (wide_pair_tile). Against eight waves of 64 x 128 over 64-byte rows
+// of B (LOAD 7), ms: 27700 rows, gate/up 19456 x 2560 4.29 -> 4.15, down
+// 2560 x 9728 2.43 -> 2.28, output projection 2560 x 2048 0.60 -> 0.57;
+// 16868 rows, gate/up 34816 x 5120 9.60 -> 9.12, down 5120 x 17408 5.15 -> 4.79.
+using PairB = GCfg<bf16, 256, 256, 128, 128, 12, 2, 3, 4>;
 // ... and 128x128 tiles (8 waves of 32x64, three 24 KB stages, two workgroups
 // per CU) for problems of few tiles whose K is too short for gemm_small.h.
 using PairS = GCfg<bf16, 128, 128, 32, 64, 7, 2, 3, 4>;
@@ -380,15 +390,15 @@ using HalfB = GCfg<f16, 256, 256, 128, 128, 11, 1, 2, 8>;
 // ... and 128x128 tiles on the LOAD 8 schedule (the last round of a large
 // launch, grouped GEMMs, and problems whose K is too short for the others).
 using HalfS = GCfg<f16, 128, 128, 32, 64, 8, 2, 3, 4>;
-// K loops that HalfB runs.
-static bool half_big_k(int K) { return K % 64 == 0 && K >= 128; }
+// K loops that the tiles of four waves run.
+static bool wide_k(int K) { return K % 64 == 0 && K >= 128; }
 // (hi, lo) fp16 pair A operands: the bf16 pair schedules with fp16 operands
-using HalfPairB = GCfg<f16, 256, 256, 64, 128, 7, 2, 3, 4>;
+using HalfPairB = GCfg<f16, 256, 256, 128, 128, 12, 2, 3, 4>;
 using HalfPairS = GCfg<f16, 128, 128, 32, 64, 7, 2, 3, 4>;
 // LM head: the 256x256 schedules transposed (F rows x 256 vocabulary rows), and
 // 64- and 128-row tiles for few rows.
 template <typename T, bool PAIR>
-using Lm = std::conditional_t<PAIR, GCfg<T, 256, 256, 64, 128, 7, 2, 3, 4, 1>,
+using Lm = std::conditional_t<PAIR, GCfg<T, 256, 256, 128, 128, 12, 2, 3, 4, 1>,
                               GCfg<T, 256, 256, 128, 128, 11, 1, 2, 8, 1>>;
 template <typename T, bool PAIR>
 using LmMid = GCfg<T, 128, 256, 64, 128, PAIR ? 7 : 8, 2, 3, 4, 1>;
@@ -525,7 +535,7 @@ hipError_t launch_gemm(int dtype, int epi, const void *A, int64_t lda, const voi
       const int c = epi == EPI_STORE_T ? -1 : small_tile_for<bf16, 2, 0>(epi, M, N, K, kBigPair);
       if (c >= 0) return small_gemm_bf16p(epi, c, gemm_args<bf16>(A, lda, B, ldb, M, N, K, 1, out, ldo, oscale), st);
       // (few tiles only where K is too short for the small tiles' ring)
-      return big_tiles >= 128 ? run_epi<PairB>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st)
+      return big_tiles >= 128 && wide_k(K) ? run_epi<PairB>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st)
                               : run_epi<PairS>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st);
     }
     if (big_tiles >= 512) return run_epi<BigB>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st);
@@ -535,12 +545,12 @@ hipError_t launch_gemm(int dtype, int epi, const void *A, int64_t lda, const voi
     if (pair) {
       const int c = epi == EPI_STORE_T ? -1 : small_tile_for<f16, 2, 0>(epi, M, N, K, kBigPair);
       if (c >= 0) return small_gemm_f16p(epi, c, gemm_args<f16>(A, lda, B, ldb, M, N, K, 1, out, ldo, oscale), st);
-      return big_tiles >= 128 ? run_epi<HalfPairB>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st)
+      return big_tiles >= 128 && wide_k(K) ? run_epi<HalfPairB>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st)
                               : run_epi<HalfPairS>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st);
     }
     const int c = small_tile_for<f16, 1, 0>(epi, M, N, K, kBigF16);
     if (c >= 0) return small_gemm_f16(epi, c, gemm_args<f16>(A, lda, B, ldb, M, N, K, 0, out, ldo, oscale), st);
-    if (big_tiles < 128 || !half_big_k(K))
+    if (big_tiles < 128 || !wide_k(K))
       return run_epi<HalfS>(epi, A, lda, B, ldb, M, N, K, 0, out, ldo, oscale, st);
     switch (epi) {
       case EPI_STORE_F32: return run_gemm_tail<HalfB, 0>(A, lda, B, ldb, M, N, K, out, ldo, oscale, st);
@@ -643,7 +653,7 @@ static hipError_t run_grouped_epi(int epi, const void *A, int64_t lda, const voi
 int gemm_group_rows(int dtype, double avg, int d, int F) {
   if (dtype == 1) return CfgF::BM;
   if (dtype != 2) return SmallB::BM;
-  if (avg >= 512.0 && half_big_k(d) && half_big_k(F)) return HalfB::BM;
+  if (avg >= 512.0 && wide_k(d) && wide_k(F)) return HalfB::BM;
   if (avg >= 64.0) return HalfS::BM;
   using S = SmallSwiglu<f16, 1, 0>;
   using P = SmallPlain<f16, 1, 0>;
@@ -701,7 +711,7 @@ static int rope_tile_for(int dtype, int qbits, int pair, int M, int N, int K) {
   return small_tile_for<f16, 1, 0>(EPI_QKV_ROPE, M, N, K, kBigF16);
 }
 static bool rope_big_ok(int dtype, int qbits, int pair, int M, int N, int K) {
-  return !qbits && (pair ? dtype == 0 || dtype == 2 : dtype == 2 && half_big_k(K)) &&
+  return !qbits && (dtype == 2 || (dtype == 0 && pair)) && wide_k(K) &&
          (int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 128;
 }
 
@@ -767,7 +777,7 @@ static hipError_t run_lmhead_rows(const void *W, const void *F, int V, int R, in
                                   hipStream_t st) {
   if (R <= 64)
     return run_lmhead<LmSmall<T, PAIR>>(W, F, V, R, K, tiles_per_split, wscale, part_m, part_s, target, zt, st);
-  if (R <= 128 || !half_big_k(K))
+  if (R <= 128 || !wide_k(K))
     return run_lmhead<LmMid<T, PAIR>>(W, F, V, R, K, tiles_per_split, wscale, part_m, part_s, target, zt, st);
   return run_lmhead<Lm<T, PAIR>>(W, F, V, R, K, tiles_per_split, wscale, part_m, part_s, target, zt, st);
 }

@@ -23,6 +23,9 @@ CASES = {
     # 256x256 tiles: two and three K steps of 64 columns, residual add, RoPE, SwiGLU
     "f16_wide": (dict(DENSE, dtype="bf16", d_model=4096, ffn=128), J.JET_F16),
     "f16_wide_ffn": (dict(DENSE, dtype="bf16", d_model=192, ffn=2112), J.JET_F16),
+    "bf16_pair_wide": (dict(DENSE, dtype="bf16", d_model=4096, ffn=128), J.JET_BF16),
+    "bf16_pair_wide_ffn": (dict(DENSE, dtype="bf16", d_model=192, ffn=2112), J.JET_BF16),
+    "f16_pair_wide": (dict(DENSE, dtype="bf16", d_model=4096, ffn=128), J.JET_F16P),
     "bf16_pair": (dict(DENSE, dtype="bf16", d_model=768, ffn=1088), J.JET_BF16),
     "f16_pair": (dict(DENSE, dtype="bf16", d_model=768, ffn=1088), J.JET_F16P),
     "q8": (dict(DENSE, dtype="q8", d_model=768, ffn=1024), J.JET_F16),
