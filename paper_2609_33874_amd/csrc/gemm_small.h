@@ -42,6 +42,12 @@ __device__ __forceinline__ void wait_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// v is in its register from here on.
+template <typename V>
+__device__ __forceinline__ void tie_reg(V &v) {
+  asm volatile("" : "+v"(v));
+}
+
 // T: operand type. NPL: planes of A (2: (hi, lo) pairs, lo K columns after
 // hi). QB: bits of a block-quantized B (0: B is T). A wave takes MI x NI
 // blocks of 16x16; WGM x WGN waves.
@@ -205,6 +211,27 @@ __device__ __forceinline__ void small_tile(const typename C::type *__restrict__ 
         for (int j = 0; j < C::NI; ++j) mma16(acc[i][j], fa[h][k][i], fb[h][k][j]);
     }
   };
+  // The compiler waits for a half's reads here, where they are the only LDS
+  // reads in flight. At their use the other half's would be too, and with
+  // direct loads in flight it waits for all of them.
+  auto arrived = [&](auto half) {
+    constexpr int h = decltype(half)::value;
+#pragma unroll
+    for (int k = 0; k < KH; ++k) {
+#pragma unroll
+      for (int i = 0; i < C::MI; ++i) tie_reg(fa[h][k][i].v);
+#pragma unroll
+      for (int j = 0; j < C::NI; ++j) {
+        if constexpr (C::QB == 0) {
+          tie_reg(fb[h][k][j].v);
+        } else {
+          tie_reg(rb[h][k][j].x);
+          if constexpr (C::QB == 8) tie_reg(rb[h][k][j].y);
+          tie_reg(sb[h][k][j]);
+        }
+      }
+    }
+  };
   // The barrier at the end of step kt certifies that every wave's loads of
   // tile kt + 1 have landed and that every wave has tile kt's fragments in
   // registers, so the loads of step kt + 1 may fill that stage. `left`: tiles
@@ -215,6 +242,7 @@ __device__ __forceinline__ void small_tile(const typename C::type *__restrict__ 
   auto step = [&](int next, auto left) {
     // (the scheduling barriers keep each half's reads ahead of the other
     // half's MFMAs; the compiler would otherwise read next to the use)
+    arrived(h0);
     read(st, h1);
     __builtin_amdgcn_sched_barrier(0);
     if (next >= 0) issue(next, sl);
