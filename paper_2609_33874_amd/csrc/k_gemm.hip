@@ -10,6 +10,7 @@
 // time of its rounds of workgroups (small_tile_for). Tiles are ordered so that
 // each XCD works on a contiguous band (see tile_coords).
 #include <algorithm>
+#include <cmath>
 
 #include "gemm_core.h"
 #include "gemm_small_tiles.h"
@@ -476,9 +477,10 @@ static hipError_t run_gemm_tail(const void *A, int64_t lda, const void *B, int64
                               (char *)out + (size_t)M1 * (size_t)ldo * osz, ldo, oscale, st);
 }
 
-// Estimated time of a launch: rounds of workgroups, one per CU.
+// Estimated time of a launch: rounds of workgroups, one per CU. Infinite (never
+// the cheapest) for a tile that cannot run this K.
 static double tile_us(const TileCost &c, int M, int N, int K) {
-  if (K % c.bk || K / c.bk < c.ahead) return 1e30;
+  if (K % c.bk || K / c.bk < c.ahead) return INFINITY;
   const int64_t tiles = (int64_t)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
   return (double)((tiles + 255) / 256) * (c.a + c.b * K / 1000.0);
 }
@@ -500,15 +502,16 @@ static int cheapest_of(int epi, int M, int N, int K, double *us) {
   return cheapest(SmallPlain<T, NPL, QB>::cost, M, N, K, us);
 }
 
-// The small tile to use for a problem, or -1 where the 256x256 tiles (big_us:
-// their cost per round, in the same model) are the cheaper ones. Those keep
-// every launch of 1024 or more such tiles: over so many rounds the last one
-// does not matter, and per element they are the fastest.
+// The small tile to use for a problem, or -1 where the 256x256 tiles (big:
+// their cost per round, in the same model; null: there are none) are the
+// cheaper ones or no small tile runs this K. The 256x256 tiles keep every
+// launch of 1024 or more such tiles: over so many rounds the last one does not
+// matter, and per element they are the fastest.
 template <typename T, int NPL, int QB>
-static int small_tile_for(int epi, int M, int N, int K, const TileCost &big) {
+static int small_tile_for(int epi, int M, int N, int K, const TileCost *big) {
   const int64_t big_tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
   if (big_tiles >= 1024) return -1;
-  double us = tile_us(big, M, N, K);
+  double us = big ? tile_us(*big, M, N, K) : INFINITY;
   return cheapest_of<T, NPL, QB>(epi, M, N, K, &us);
 }
 
@@ -532,7 +535,7 @@ hipError_t launch_gemm(int dtype, int epi, const void *A, int64_t lda, const voi
   const int64_t big_tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
   if (dtype == 0) {
     if (pair) {
-      const int c = epi == EPI_STORE_T ? -1 : small_tile_for<bf16, 2, 0>(epi, M, N, K, kBigPair);
+      const int c = epi == EPI_STORE_T ? -1 : small_tile_for<bf16, 2, 0>(epi, M, N, K, &kBigPair);
       if (c >= 0) return small_gemm_bf16p(epi, c, gemm_args<bf16>(A, lda, B, ldb, M, N, K, 1, out, ldo, oscale), st);
       // (few tiles only where K is too short for the small tiles' ring)
       return big_tiles >= 128 && wide_k(K) ? run_epi<PairB>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st)
@@ -543,12 +546,12 @@ hipError_t launch_gemm(int dtype, int epi, const void *A, int64_t lda, const voi
   }
   if (dtype == 2) {
     if (pair) {
-      const int c = epi == EPI_STORE_T ? -1 : small_tile_for<f16, 2, 0>(epi, M, N, K, kBigPair);
+      const int c = epi == EPI_STORE_T ? -1 : small_tile_for<f16, 2, 0>(epi, M, N, K, &kBigPair);
       if (c >= 0) return small_gemm_f16p(epi, c, gemm_args<f16>(A, lda, B, ldb, M, N, K, 1, out, ldo, oscale), st);
       return big_tiles >= 128 && wide_k(K) ? run_epi<HalfPairB>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st)
                               : run_epi<HalfPairS>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st);
     }
-    const int c = small_tile_for<f16, 1, 0>(epi, M, N, K, kBigF16);
+    const int c = small_tile_for<f16, 1, 0>(epi, M, N, K, &kBigF16);
     if (c >= 0) return small_gemm_f16(epi, c, gemm_args<f16>(A, lda, B, ldb, M, N, K, 0, out, ldo, oscale), st);
     if (big_tiles < 128 || !wide_k(K))
       return run_epi<HalfS>(epi, A, lda, B, ldb, M, N, K, 0, out, ldo, oscale, st);
@@ -590,7 +593,7 @@ hipError_t launch_gemm_q8(int epi, const void *A, int64_t lda, const void *Bq, c
                           int K, void *out, int64_t ldo, float oscale, hipStream_t st) {
   if (M <= 0 || N <= 0) return hipSuccess;
   if (K % 32 != 0) return hipErrorInvalidValue;
-  const int c = epi == EPI_STORE_T ? -1 : small_tile_for<f16, 1, 8>(epi, M, N, K, kBigQ);
+  const int c = epi == EPI_STORE_T ? -1 : small_tile_for<f16, 1, 8>(epi, M, N, K, &kBigQ);
   if (c >= 0)
     return small_gemm_q8(epi, c, gemm_args<f16>(A, lda, Bq, (int64_t)K * 8 / 8, M, N, K, 0, out, ldo, oscale, Bs), st);
   const int64_t big_tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
@@ -602,7 +605,7 @@ hipError_t launch_gemm_q4(int epi, const void *A, int64_t lda, const void *Bq, c
                           int K, void *out, int64_t ldo, float oscale, hipStream_t st) {
   if (M <= 0 || N <= 0) return hipSuccess;
   if (K % 32 != 0) return hipErrorInvalidValue;
-  const int c = epi == EPI_STORE_T ? -1 : small_tile_for<f16, 1, 4>(epi, M, N, K, kBigQ);
+  const int c = epi == EPI_STORE_T ? -1 : small_tile_for<f16, 1, 4>(epi, M, N, K, &kBigQ);
   if (c >= 0)
     return small_gemm_q4(epi, c, gemm_args<f16>(A, lda, Bq, (int64_t)K * 4 / 8, M, N, K, 0, out, ldo, oscale, Bs), st);
   const int64_t big_tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
@@ -702,13 +705,15 @@ static hipError_t run_qkv_rope(const void *A, int64_t lda, const void *B, int64_
 }
 
 // Small RoPE tile for a problem (-1: none), and whether the 256x256 tiles,
-// whose waves of 128 columns hold a head each, can run it.
+// whose waves of 128 columns hold a head each, can run it. Neither: the
+// projection and the rotation run as two kernels (block-quantized B of K = 128,
+// shorter than the ring of any small tile, or of 1024 256x256 tiles and more).
 static int rope_tile_for(int dtype, int qbits, int pair, int M, int N, int K) {
-  if (qbits == 8) return small_tile_for<f16, 1, 8>(EPI_QKV_ROPE, M, N, K, TileCost{256, 256, 32, 1, 1e30, 0});
-  if (qbits == 4) return small_tile_for<f16, 1, 4>(EPI_QKV_ROPE, M, N, K, TileCost{256, 256, 32, 1, 1e30, 0});
-  if (dtype == 0) return pair ? small_tile_for<bf16, 2, 0>(EPI_QKV_ROPE, M, N, K, kBigPair) : -1;
-  if (pair) return small_tile_for<f16, 2, 0>(EPI_QKV_ROPE, M, N, K, kBigPair);
-  return small_tile_for<f16, 1, 0>(EPI_QKV_ROPE, M, N, K, kBigF16);
+  if (qbits == 8) return small_tile_for<f16, 1, 8>(EPI_QKV_ROPE, M, N, K, nullptr);
+  if (qbits == 4) return small_tile_for<f16, 1, 4>(EPI_QKV_ROPE, M, N, K, nullptr);
+  if (dtype == 0) return pair ? small_tile_for<bf16, 2, 0>(EPI_QKV_ROPE, M, N, K, &kBigPair) : -1;
+  if (pair) return small_tile_for<f16, 2, 0>(EPI_QKV_ROPE, M, N, K, &kBigPair);
+  return small_tile_for<f16, 1, 0>(EPI_QKV_ROPE, M, N, K, &kBigF16);
 }
 static bool rope_big_ok(int dtype, int qbits, int pair, int M, int N, int K) {
   return !qbits && (dtype == 2 || (dtype == 0 && pair)) && wide_k(K) &&

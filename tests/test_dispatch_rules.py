@@ -1,0 +1,41 @@
+"""Rules of the GEMM dispatch that need no GPU: a fused kernel is chosen only
+for problems that one of its tiles can run."""
+import ctypes
+import itertools
+
+import pytest
+
+from paper_2609_33874_amd import jet as J
+
+# jetk::gemm_qkv_rope_ok(dtype, qbits, pair, M, N, K, head_dim)
+ROPE_OK = "_ZN4jetk16gemm_qkv_rope_okEiiiiiii"
+BF16, FP32, F16 = 0, 1, 2
+ROWS = [1, 16, 63, 257, 1000, 4000, 12800, 13056, 15360, 26000, 40000, 52224, 52480, 70000]
+COLS = [384, 640, 1280, 2048, 7168]
+
+
+def rope_ok(*args):
+    f = getattr(J.lib(), ROPE_OK)
+    f.restype = ctypes.c_bool
+    return f(*map(ctypes.c_int, args))
+
+
+@pytest.mark.parametrize("dtype,qbits,pair,k_step,k_min", [
+    # the shortest ring of a small tile: three stages of 128 columns (block-
+    # quantized B) or three of 64; the 256x256 tiles need two steps of 64
+    (F16, 8, 0, 128, 256), (F16, 4, 0, 128, 256), (F16, 0, 0, 64, 128), (F16, 0, 1, 64, 128), (BF16, 0, 1, 64, 128)])
+def test_fused_rope_only_where_a_tile_runs_k(dtype, qbits, pair, k_step, k_min):
+    taken = 0
+    for M, N, K in itertools.product(ROWS, COLS, [32, 64, 96, 128, 192, 256, 320, 384, 1536]):
+        if rope_ok(dtype, qbits, pair, M, N, K, 128):
+            taken += 1
+            assert K % k_step == 0 and K >= k_min, (M, N, K)
+    assert taken > 100  # the rule is not simply "never"
+
+
+def test_fused_rope_refuses_other_forms():
+    for M, N, K in itertools.product(ROWS, COLS, [256, 1536]):
+        assert not rope_ok(FP32, 0, 0, M, N, K, 128)  # no fused fp32 kernel
+        assert not rope_ok(BF16, 0, 0, M, N, K, 128)  # nor one for single bf16 planes
+        for hd in (32, 64):  # waves hold both dims of a rotation pair for head_dim 128 only
+            assert not rope_ok(F16, 0, 0, M, N, K, hd)

@@ -30,6 +30,9 @@ CASES = {
     "f16_pair": (dict(DENSE, dtype="bf16", d_model=768, ffn=1088), J.JET_F16P),
     "q8": (dict(DENSE, dtype="q8", d_model=768, ffn=1024), J.JET_F16),
     "q4": (dict(DENSE, dtype="q4", d_model=768, ffn=1024), J.JET_F16),
+    # the narrowest block-quantized models: no fused QKV tile runs K = 128
+    "q8_narrow": (dict(DENSE, dtype="q8", d_model=128, ffn=192), J.JET_F16),
+    "q4_narrow": (dict(DENSE, dtype="q4", d_model=128, ffn=192), J.JET_F16),
     "hybrid_pair": (dict(DENSE, arch="hybrid", n_layers=4, dtype="bf16", d_model=640, ffn=832, gdn_heads=5,
                          gdn_dk=128, gdn_dv=128, conv_kernel=4), J.JET_BF16),
     # the stepwise recurrence over prefixes (chunks of 32 steps)
