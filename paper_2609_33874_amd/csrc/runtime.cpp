@@ -1478,10 +1478,15 @@ void wave_bytes_bound(const jet_model *m, double *per_row, double *fixed) {
   }
   if (h.n_experts) {
     const double k = (double)h.top_k, E = (double)h.n_experts, Fe = (double)h.moe_ffn, Fs = (double)h.shared_ffn;
-    const double bm = (double)jetk::gemm_group_rows_max(m->kdt), bm_min = 16.0;
+    // Counted for tiles of the most rows a launch may take. Tiles of 16 or 64
+    // rows (up to 64 rows an expert) or 128 make the table of tiles longer, by
+    // at most 4 bytes an expert or per 128 routed rows, and the segments'
+    // padding shorter by at least 128 rows of (2 d + Fe) elements an expert,
+    // which is more than the table of all rows that the scratch can hold.
+    const double bm = (double)jetk::gemm_group_rows_max(m->kdt);
     int64_t n_router = 0;
     for (const Layer &ly : m->layers) n_router = std::max(n_router, ly.n_router);
-    r += (double)n_router * 4 + 3 * k * 4 + (k / bm_min) * 4 + 2 * E * 4 * k / jetk::kMoeChunk;
+    r += (double)n_router * 4 + 3 * k * 4 + (k / bm) * 4 + 2 * E * 4 * k / jetk::kMoeChunk;
     r += k * (2 * d + Fe) * esz;          // routed rows: gathered input, hidden, output
     r += 4 + Fs * esz + d * 4;            // shared expert
     f += (E * bm + bm) * (2 * d + Fe) * esz + 4 * (E + 2) + 2 * E * 4;

@@ -117,3 +117,28 @@ def test_noalloc_capacity_error_then_next_call(model_dir):
         check("after a refused call", wl, ref, got, J.JET_F16)
     finally:
         J.jet_model_free(m)
+
+
+@pytest.mark.parametrize("dtype,longest", [(J.JET_F16, 11039), (J.JET_FP32, 6476), (J.JET_BF16_SINGLE, 11039)])
+def test_noalloc_longest_candidate_with_experts(dtype, longest, tmp_path):
+    """The longest candidate that the scratch takes with this expert model
+    (8 experts, all chosen) stays accepted, and scores as outside the scratch.
+    The bound on a row's buffers decides it: two bytes a row more refuse the
+    last few tokens."""
+    path = str(tmp_path / "m.jetm")
+    jet_synth.write_model(path, dict(arch="dense", dtype="bf16", d_model=64, n_layers=2, n_heads=1, n_kv_heads=1,
+                                     head_dim=64, ffn=64, vocab=256, n_experts=8, top_k=8, moe_ffn=64, shared_ffn=64,
+                                     max_ctx=32768))
+    wl = jet_synth.from_lists([np.arange(5, dtype=np.int32)], [[(np.arange(longest) % 256).astype(np.int32)]])
+    m = J.jet_model_load(path, dtype=dtype)
+    try:
+        p = J.jet_prefill_prefix(m, wl.prefix_offsets, wl.prefix_tokens)
+        try:
+            ref, got = both(m, p, wl)
+        finally:
+            J.jet_prefix_free(p)
+        # every launch has the same rows inside the scratch and outside
+        np.testing.assert_array_equal(got[0], ref[0])
+        np.testing.assert_array_equal(got[1], ref[1])
+    finally:
+        J.jet_model_free(m)
