@@ -26,6 +26,18 @@ struct GemmArgs {
   const uint16_t *Bs = nullptr;
 };
 
+// silu(gate) * up, silu(g) = g / (1 + e^-g) with the hardware reciprocal (~1
+// ulp). PAIR (the result is split into a (hi, lo) pair): the product is rounded
+// before the remainder v - hi is taken from it. Left to the compiler, a fused
+// multiply-subtract may take it from the unrounded product in one kernel and
+// not in another, and a row's last bits would depend on its tile.
+template <bool PAIR>
+__device__ __forceinline__ float swiglu(float gate, float up) {
+  float v = gate * __builtin_amdgcn_rcpf(1.0f + __expf(-gate)) * up;
+  if constexpr (PAIR) asm("" : "+v"(v));
+  return v;
+}
+
 // (hi, lo) split of v stored at p[0] and p[ps] (lo only with pair).
 template <typename T>
 __device__ __forceinline__ void put_split(T *p, int64_t ps, float v, int pair) {

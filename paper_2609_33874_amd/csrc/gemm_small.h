@@ -300,8 +300,7 @@ __global__ __launch_bounds__(C::NT) void gemm_small_kernel(GemmArgs<typename C::
           const int col = small_col<C, 2>(wn, j), gcol = n0 + (col & ~63);  // first column of the gate block
           if (gcol >= g.N) continue;
           const int f = (gcol >> 6) * 32 + (col & 31) + (lane & 15);
-          const float gt = acc[i][j][e] * g.oscale, up = acc[i][j + 1][e] * g.oscale;
-          const float v = gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * up;
+          const float v = swiglu<C::NPL == 2>(acc[i][j][e] * g.oscale, acc[i][j + 1][e] * g.oscale);
           put_split<T>((T *)g.out + (int64_t)row * g.ldo + f, g.N >> 1, v, g.pair_out);
         }
       } else if constexpr (EPI == 4) {

@@ -124,12 +124,7 @@ __device__ __forceinline__ bool staged_epilogue(const GemmArgs<typename C::type>
         for (int jp = 0; jp < C::NI / 2; ++jp)
 #pragma unroll
           for (int e = 0; e < 16; ++e) {
-            const float gt = acc[i][2 * jp][e] * g.oscale, up = acc[i][2 * jp + 1][e] * g.oscale;
-            // silu(g) = g / (1 + e^-g) with the hardware reciprocal (~1 ulp)
-            float v = gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * up;
-            // the remainder is of the rounded product, as in every other tile
-            // (not a fused multiply-subtract)
-            if constexpr (C::PAIRA) asm("" : "+v"(v));
+            const float v = swiglu<C::PAIRA>(acc[i][2 * jp][e] * g.oscale, acc[i][2 * jp + 1][e] * g.oscale);
             const int r = 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
             const T hi = from_f<T>(v);
             wl[r * LDH + jp * 32 + (lane & 31)] = hi;
@@ -223,12 +218,8 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(GemmArgs<typename C::type> 
         for (int e = 0; e < 16; ++e) {
           const int row = m0 + wm * C::WM + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
           if (row < g.M && gcol < g.N) {
-            const float gt = acc[i][2 * jp][e] * g.oscale, up = acc[i][2 * jp + 1][e] * g.oscale;
-            // silu(g) = g / (1 + e^-g) with the hardware reciprocal (~1 ulp)
-            const float v = gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * up;
-            const T hi = from_f<T>(v);
-            out[(int64_t)row * g.ldo + f] = hi;
-            if (g.pair_out) out[(int64_t)row * g.ldo + (g.N >> 1) + f] = from_f<T>(v - to_f<T>(hi));
+            const float v = swiglu<C::PAIRA>(acc[i][2 * jp][e] * g.oscale, acc[i][2 * jp + 1][e] * g.oscale);
+            put_split<T>(out + (int64_t)row * g.ldo + f, g.N >> 1, v, g.pair_out);
           }
         }
       }
