@@ -7,15 +7,20 @@
 // at many items the matrix cores and the LDS reads of K and V. Passing tiles
 // through registers (one tile ahead, V transposed element by element on the way
 // to the LDS, two barriers per tile) took 2.3-3 us per tile. Here
-//   * K and V rows go straight into a ring of NS stages, NS - 1 tiles in
-//     flight, one barrier per tile; own-candidate tiles are part of the same
+//   * K and V rows go straight into one of two stages while the other is
+//     computed, one barrier per tile; own-candidate tiles are part of the same
 //     stream;
 //   * V stays row-major and is read transposed (ds_read_b64_tr_b16).
+// Two stages of 32 KB let two workgroups share a CU, one's chain under the
+// other's. A ring of four (one workgroup per CU, three tiles in flight) is no
+// faster even where every workgroup has a CU of its own: 12 query heads, 2 KV
+// heads, candidates' launch with K and V evicted between calls, us: one question
+// of 731 keys (12 items) 24.9 with four stages, 23.9 with two; 16 questions
+// of 700 (192 items) 24.8 and 23.7; past 256 items it runs a second round: 132
+// questions of 700 (264 items) 53.1 and 33.0.
 // A workgroup of NW waves takes 16 QB NW query slots of one (question, KV
-// head); every query runs the same operations in the same order whatever QB,
-// NW and NS are, so a candidate rounds alike in any batch.
-#include <algorithm>
-
+// head); every query runs the same operations in the same order whatever QB
+// and NW are, so a candidate rounds alike in any batch.
 #include "attn_common.h"
 #include "gemm_core.h"
 
@@ -45,12 +50,12 @@ __device__ __forceinline__ float group_max(float v) {
   return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
-template <typename T, int MODE, int QB, int NW, int NS>
+template <typename T, int MODE, int QB, int NW>
 __global__ __launch_bounds__(64 * NW, 2) void attn16_kernel(AttnArgs a) {
   constexpr int HD = 128, KT = 64, BLOCK = 16 * QB * NW;
   constexpr int PLANE = KT * HD * 2, STAGE = 2 * PLANE;  // bytes: K, then V
-  constexpr int LD = KT / 4 / NW, PT = 2 * LD;            // direct loads per wave: of K or V, per tile
-  static_assert(KT / 4 % NW == 0 && PT * (NS - 1) < 64, "loads per wave");
+  constexpr int LD = KT / 4 / NW;                          // direct loads per wave of a tile of K or V
+  static_assert(KT / 4 % NW == 0, "whole loads per wave");
   extern __shared__ __align__(16) char smem[];
 
   const AttnItem it = a.items[blockIdx.x];
@@ -116,15 +121,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn16_kernel(AttnArgs a) {
                                        0);
     }
   };
-  Tile cur{-1, 0, min(KT, npre)}, ahead = cur;  // (every prefix has a key)
-  int flight = 0;  // tiles issued and not yet waited for
-#pragma unroll
-  for (int s = 0; s < NS - 1; ++s)
-    if (ahead.nk > 0) {
-      issue(ahead, s);
-      ahead = next_tile(ahead);
-      ++flight;
-    }
+  Tile cur{-1, 0, min(KT, npre)};  // (every prefix has a key)
+  if (cur.nk > 0) issue(cur, 0);
+  Tile ahead = next_tile(cur);
 
   bool valid[QB];
   int row[QB], head[QB], qi[QB], first[QB];
@@ -169,23 +168,21 @@ __global__ __launch_bounds__(64 * NW, 2) void attn16_kernel(AttnArgs a) {
   const int vrow = 4 * g + (l16 >> 2), vsw = (vrow & 7) << 5;
   const uint32_t voff = lds0 + PLANE + vrow * 256 + ((l16 >> 1) & 1) * 16 + (l16 & 1) * 8;
 
-  // Q has arrived (with it the first tiles, which were issued before it): the
+  // Q has arrived (with it the first tile, which was issued before it): the
   // compiler would otherwise wait for every load in flight at each use of Q in
   // the loop
   __builtin_amdgcn_s_waitcnt(0 | 7 << 4 | 15 << 8);
-  int stage = 0, fill = NS - 1;
+  int stage = 0;
   while (cur.nk > 0) {
     // this tile has landed (own loads; with the barrier every wave's), and
-    // every wave is done with the stage that is filled next
-    wait_tiles<PT, NS - 2>(flight - 1);
+    // every wave is done with the other stage, which is filled next
+    wait_vmcnt<0>();
     wait_lgkmcnt0();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    --flight;
     if (ahead.nk > 0) {
-      issue(ahead, fill);
+      issue(ahead, stage ^ 1);
       ahead = next_tile(ahead);
-      ++flight;
     }
     const int nk = cur.nk;
     if (!idle) {
@@ -331,8 +328,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn16_kernel(AttnArgs a) {
       }
     }
     cur = next_tile(cur);
-    stage = stage + 1 == NS ? 0 : stage + 1;
-    fill = fill + 1 == NS ? 0 : fill + 1;
+    stage ^= 1;
   }
 
 #pragma unroll
@@ -354,26 +350,18 @@ __global__ __launch_bounds__(64 * NW, 2) void attn16_kernel(AttnArgs a) {
   }
 }
 
-template <typename T, int MODE, int QB, int NW, int NS>
+template <typename T, int MODE, int QB>
 static hipError_t run16(const AttnArgs &a, hipStream_t st) {
-  constexpr int lds = NS * 2 * 64 * 256;
-  static const hipError_t once =
-      lds <= 65536 ? hipSuccess
-                   : hipFuncSetAttribute((const void *)attn16_kernel<T, MODE, QB, NW, NS>,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  if (once != hipSuccess) return once;
-  hipLaunchKernelGGL((attn16_kernel<T, MODE, QB, NW, NS>), dim3(a.n_items), dim3(64 * NW), lds, st, a);
+  constexpr int NW = 4, lds = 2 * 2 * 64 * 256;
+  static_assert(lds <= 65536, "within the default limit, two workgroups per CU");
+  hipLaunchKernelGGL((attn16_kernel<T, MODE, QB, NW>), dim3(a.n_items), dim3(64 * NW), lds, st, a);
   return hipGetLastError();
 }
 
-// Items that leave CUs empty take a deep ring (one workgroup per CU); more
-// items a shallow one, so that two workgroups share a CU and one's chain runs
-// under the other's.
 template <typename T, int MODE>
 static hipError_t run16_block(const AttnArgs &a, hipStream_t st) {
-  const bool deep = a.n_items <= 384;
-  if (a.block == 64) return deep ? run16<T, MODE, 1, 4, 4>(a, st) : run16<T, MODE, 1, 4, 2>(a, st);
-  if (a.block == 128) return deep ? run16<T, MODE, 2, 4, 4>(a, st) : run16<T, MODE, 2, 4, 2>(a, st);
+  if (a.block == 64) return run16<T, MODE, 1>(a, st);
+  if (a.block == 128) return run16<T, MODE, 2>(a, st);
   return hipErrorInvalidValue;
 }
 
