@@ -374,9 +374,8 @@ using SmallB = GCfg<bf16, 256, 128, 64, 64, 2, 1, 3, 8>;
 using CfgF = GCfg<float, 128, 128, 64, 64, 0, 1>;
 // fp16 operands: 256x256 tiles of four waves (wide_tile). Against eight waves
 // of 64 x 128 over 64-byte rows (LOAD 8), 67007 rows, ms: gate/up 17920 x 1536
-// 3.50 -> 3.39, down 1536 x 8960 2.01 -> 1.73, QKV 2048 x 1536 0.53 -> 0.47;
-// output projection 1536 x 1536 0.49 (256x128 tiles, two workgroups per CU)
-// -> 0.46. Without the direct loads the down projection takes 1.57, without
+// 3.50 -> 3.39, down 1536 x 8960 2.01 -> 1.73; output projection 1536 x 1536
+// 0.49 (256x128 tiles, two workgroups per CU) -> 0.46. Without the direct loads the down projection takes 1.57, without
 // the fragment reads too 1.43 (a power-limited MFMA rate).
 using HalfB = GCfg<f16, 256, 256, 128, 128, 11, 1, 2, 8>;
 // ... and 128x128 tiles on the LOAD 8 schedule (the last round of a large
@@ -387,6 +386,14 @@ static bool wide_k(int K) { return K % 64 == 0 && K >= 128; }
 // (hi, lo) fp16 pair A operands: the bf16 pair schedules with fp16 operands
 using HalfPairB = GCfg<f16, 256, 256, 128, 128, 12, 2, 3, 4>;
 using HalfPairS = GCfg<f16, 128, 128, 32, 64, 7, 2, 3, 4>;
+// 256x256 tiles of eight waves of 64 x 128, two per SIMD, for work that one wave
+// per SIMD cannot hide behind another's: the RoPE epilogue, whose loads of
+// positions and angles and 2-byte stores it waits for. QKV of 2048 x 1536, us with eight waves and
+// with four: 57600 rows fp16 530 and 657, pairs 805 and 943; 67000 rows 590 and
+// 750, 905 and 1072.
+using HalfE = GCfg<f16, 256, 256, 64, 128, 8, 2, 3, 4>;
+using PairE = GCfg<bf16, 256, 256, 64, 128, 7, 2, 3, 4>;
+using HalfPairE = GCfg<f16, 256, 256, 64, 128, 7, 2, 3, 4>;
 // LM head: the 256x256 schedules transposed (F rows x 256 vocabulary rows), and
 // 64- and 128-row tiles for few rows.
 template <typename T, bool PAIR>
@@ -706,14 +713,14 @@ static int rope_tile_for(int dtype, int qbits, int pair, int M, int N, int K) {
   if (pair) return small_tile_for<f16, 2, 0>(EPI_QKV_ROPE, M, N, K, &kBigPair);
   return small_tile_for<f16, 1, 0>(EPI_QKV_ROPE, M, N, K, &kBigF16);
 }
-static bool rope_big_ok(int dtype, int qbits, int pair, int M, int N, int K) {
-  return !qbits && (dtype == 2 || (dtype == 0 && pair)) && wide_k(K) &&
+static bool rope_big_ok(int dtype, int qbits, int pair, int M, int N) {
+  return !qbits && (dtype == 2 || (dtype == 0 && pair)) &&
          (int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 128;
 }
 
 bool gemm_qkv_rope_ok(int dtype, int qbits, int pair, int M, int N, int K, int head_dim) {
   if (head_dim != 128 || N % 128 || M <= 0 || dtype == 1) return false;
-  return rope_tile_for(dtype, qbits, pair, M, N, K) >= 0 || rope_big_ok(dtype, qbits, pair, M, N, K);
+  return rope_tile_for(dtype, qbits, pair, M, N, K) >= 0 || rope_big_ok(dtype, qbits, pair, M, N);
 }
 
 hipError_t launch_gemm_qkv_rope(int dtype, int qbits, const void *A, int64_t lda, const void *B, const uint16_t *Bs,
@@ -734,9 +741,9 @@ hipError_t launch_gemm_qkv_rope(int dtype, int qbits, const void *A, int64_t lda
     if (qbits == 4) return small_gemm_q4(EPI_QKV_ROPE, c, g, st);
     return pair ? small_gemm_f16p(EPI_QKV_ROPE, c, g, st) : small_gemm_f16(EPI_QKV_ROPE, c, g, st);
   }
-  if (dtype == 0) return run_qkv_rope<PairB>(A, lda, B, ldb, M, N, K, pair, oscale, r, st);
-  if (pair) return run_qkv_rope<HalfPairB>(A, lda, B, ldb, M, N, K, pair, oscale, r, st);
-  return run_qkv_rope<HalfB>(A, lda, B, ldb, M, N, K, 0, oscale, r, st);
+  if (dtype == 0) return run_qkv_rope<PairE>(A, lda, B, ldb, M, N, K, pair, oscale, r, st);
+  if (pair) return run_qkv_rope<HalfPairE>(A, lda, B, ldb, M, N, K, pair, oscale, r, st);
+  return run_qkv_rope<HalfE>(A, lda, B, ldb, M, N, K, 0, oscale, r, st);
 }
 
 void lmhead_plan(int dtype, int V, int R, int *tiles_per_split, int *nsplit) {

@@ -22,8 +22,8 @@ def rope_ok(*args):
 
 @pytest.mark.parametrize("dtype,qbits,pair,k_step,k_min", [
     # the shortest ring of a small tile: three stages of 128 columns (block-
-    # quantized B) or three of 64; the 256x256 tiles need two steps of 64
-    (F16, 8, 0, 128, 256), (F16, 4, 0, 128, 256), (F16, 0, 0, 64, 128), (F16, 0, 1, 64, 128), (BF16, 0, 1, 64, 128)])
+    # quantized B); the 256x256 tiles of the other kinds run any K of whole steps
+    (F16, 8, 0, 128, 256), (F16, 4, 0, 128, 256), (F16, 0, 0, 32, 32), (F16, 0, 1, 32, 32), (BF16, 0, 1, 32, 32)])
 def test_fused_rope_only_where_a_tile_runs_k(dtype, qbits, pair, k_step, k_min):
     taken = 0
     for M, N, K in itertools.product(ROWS, COLS, [32, 64, 96, 128, 192, 256, 320, 384, 1536]):
