@@ -257,17 +257,26 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(GemmArgs<typename C::type> 
 template <class C>
 __global__ __launch_bounds__(C::NT) void lmhead_lse_kernel(const typename C::type *__restrict__ W,
                                                           const typename C::type *__restrict__ F, int V, int R,
-                                                          int K, int tiles_per_split, int nsplit, float zscale,
+                                                          int K, int tiles_per_split, int nsplit, int strided,
+                                                          float zscale,
                                                           float *__restrict__ part_m, float *__restrict__ part_s,
                                                           const int32_t *__restrict__ target,
                                                           float *__restrict__ zt) {
   extern __shared__ uint4 lds[];
-  // Workgroups go round-robin to the 8 XCDs: XCD x takes the splits x, x + 8,
-  // .., each with all its row tiles in a row, so a vocabulary tile is read
-  // into one L2 only.
-  const int nrt = (R + C::BM - 1) / C::BM;
-  const int seq = blockIdx.x >> 3, split = (seq / nrt) * 8 + (blockIdx.x & 7), m0 = (seq % nrt) * C::BM;
-  if (split >= nsplit) return;
+  // Workgroups go round-robin to the 8 XCDs. strided: XCD x takes the splits
+  // x, x + 8, .., each with all its row tiles in a row, so a vocabulary tile is
+  // read into one L2 only and the XCDs walk the row tiles in step. Else each
+  // XCD takes a band of the (split, row tile) pairs, even to one workgroup.
+  const int nrt = (R + C::BM - 1) / C::BM, id = blockIdx.x, per = nsplit * nrt / 8;
+  int split, rt;
+  if (strided) {
+    split = (id >> 3) / nrt * 8 + (id & 7), rt = (id >> 3) % nrt;
+    if (split >= nsplit) return;
+  } else {
+    const int seq = id < per * 8 ? (id & 7) * per + (id >> 3) : id;
+    split = seq / nrt, rt = seq % nrt;
+  }
+  const int m0 = rt * C::BM;
   const int ntiles = (V + C::BN - 1) / C::BN;
   const int vt0 = split * tiles_per_split, vt1 = min(vt0 + tiles_per_split, ntiles);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -403,6 +412,9 @@ template <typename T, bool PAIR>
 using LmMid = GCfg<T, 128, 256, 64, 128, PAIR ? 7 : 8, 2, 3, 4, 1>;
 template <typename T, bool PAIR>
 using LmSmall = GCfg<T, 64, 256, 64, 128, PAIR ? 7 : 8, 2, 4, 4, 1>;
+// ... and single planes on 256x256 tiles of eight waves (run_lmhead_rows).
+template <typename T>
+using LmE = GCfg<T, 256, 256, 64, 128, 8, 2, 3, 4, 1>;
 using LmF = GCfg<float, 128, 128, 64, 64, 0, 1, 2, 8, 1>;
 // int8 B operand (block-quantized weights): the LOAD 8 schedule with int8 B
 // tiles and per-block scales (three 24.5 KB stages), 256x256 tiles of 8
@@ -766,22 +778,42 @@ static hipError_t run_lmhead(const void *W, const void *F, int V, int R, int K, 
   if (once != hipSuccess) return once;
   const int nsplit = ((V + C::BN - 1) / C::BN + tiles_per_split - 1) / tiles_per_split;
   const int nrt = (R + C::BM - 1) / C::BM;
-  hipLaunchKernelGGL((lmhead_lse_kernel<C>), dim3((nsplit + 7) / 8 * 8 * nrt), dim3(C::NT), C::LDS_BYTES, st,
-                     (const T *)W, (const T *)F, V, R, K, tiles_per_split, nsplit, wscale * kLog2e, part_m, part_s,
-                     target, zt);
+  // Splits dealt to the XCDs whole leave some with one more than others: only
+  // where that costs no further round of 32 workgroups an XCD. (fp16, us, whole
+  // splits and even bands: 2560 x 151936, 6400 rows, 30 rounds both 3856 and
+  // 4115; 1500 rows, 8 rounds and 7 984 and 914; 2560 x 40000, 3328 rows, 9 and
+  // 8 573 and 539.)
+  const int per_xcd = (nsplit + 7) / 8 * nrt, strided = (per_xcd + 31) / 32 <= (nsplit * nrt + 255) / 256;
+  hipLaunchKernelGGL((lmhead_lse_kernel<C>), dim3(strided ? per_xcd * 8 : nsplit * nrt), dim3(C::NT), C::LDS_BYTES, st,
+                     (const T *)W, (const T *)F, V, R, K, tiles_per_split, nsplit, strided, wscale * kLog2e, part_m,
+                     part_s, target, zt);
   return hipGetLastError();
 }
 
-// The row tile: the fewest rounds of full tiles. 64 rows and 128 rows are
-// bound by the stream of W, not by the matrix cores.
+// The row tile: 64 rows up to 64 and 128 up to 128, where the launch is bound by
+// the stream of W and not by the matrix cores; above, 256. Single planes take
+// the tiles of four waves there for a long K and more than one workgroup per CU
+// (151936 x 2560: 1000 rows 636 us, 714 with eight waves, 6400 rows 3856 and
+// 4429; 40000 x 2560, 512 rows 125 and 125), else those of eight, two per SIMD,
+// whose exponentials do not wait for each other (four and eight waves: 40000 x
+// 896, 1000 rows 102 and 80; 151936 x 128, 6400 rows 826 and 531; 40000 x 2560,
+// 129 rows 65 and 59; 151936 x 1536, 1500 rows 684 and 624, 6400 rows 2713 and
+// 2577). Pairs always (151936 x 128, 6400 rows 1119 against 1110).
 template <typename T, bool PAIR>
 static hipError_t run_lmhead_rows(const void *W, const void *F, int V, int R, int K, int tiles_per_split,
                                   float wscale, float *part_m, float *part_s, const int32_t *target, float *zt,
                                   hipStream_t st) {
   if (R <= 64)
     return run_lmhead<LmSmall<T, PAIR>>(W, F, V, R, K, tiles_per_split, wscale, part_m, part_s, target, zt, st);
-  if (R <= 128 || !wide_k(K))
+  if (R <= 128)
     return run_lmhead<LmMid<T, PAIR>>(W, F, V, R, K, tiles_per_split, wscale, part_m, part_s, target, zt, st);
+  if constexpr (!PAIR) {
+    const int groups = ((V + 255) / 256 + tiles_per_split - 1) / tiles_per_split * ((R + 255) / 256);
+    if (K < 2048 || groups <= 256)
+      return run_lmhead<LmE<T>>(W, F, V, R, K, tiles_per_split, wscale, part_m, part_s, target, zt, st);
+  } else if (K % 64 || K < 128) {
+    return run_lmhead<LmMid<T, PAIR>>(W, F, V, R, K, tiles_per_split, wscale, part_m, part_s, target, zt, st);
+  }
   return run_lmhead<Lm<T, PAIR>>(W, F, V, R, K, tiles_per_split, wscale, part_m, part_s, target, zt, st);
 }
 

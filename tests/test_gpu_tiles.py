@@ -143,3 +143,36 @@ def test_long_candidates(heads, kv_heads, mode, tmp_path):
     err = np.max(np.abs(np.concatenate(alone) - ref_tok))
     print(f"[long] heads {heads}/{kv_heads} mode {mode}: max|d tok|={err:.3e}", flush=True)
     assert err <= (1e-4 if mode == J.JET_BF16 else 2e-2)
+
+
+@pytest.mark.parametrize("mode,d,vocab", [
+    (J.JET_F16, 320, 1100), (J.JET_BF16, 256, 1100),
+    # 83 vocabulary splits: 700 rows are dealt to the XCDs in even bands
+    (J.JET_F16, 320, 21000),
+    # above 128 rows: tiles of eight waves up to 256 workgroups, of four from there
+    (J.JET_F16, 2048, 40000), (J.JET_BF16_SINGLE, 2048, 40000)])
+def test_lm_head_does_not_depend_on_the_rows(mode, d, vocab, tmp_path):
+    """One-token candidates: the call is the LM head alone, one row each. 35,
+    105, 210, 315 and 700 rows take its 64-, 128- and 256-row tiles."""
+    path = str(tmp_path / "m.jetm")
+    jet_synth.write_model(path, dict(arch="dense", dtype="bf16", n_layers=1, n_heads=1, n_kv_heads=1, head_dim=64,
+                                     d_model=d, ffn=64, vocab=vocab, max_ctx=64))
+    g = np.random.Generator(np.random.Philox(key=[7, d]))
+    pre = [g.integers(0, vocab, 3 + q % 4).astype(np.int32) for q in range(20)]
+    cand = [[y for y in g.integers(0, vocab, (35, 1)).astype(np.int32)] for _ in pre]
+    m = J.jet_model_load(path, dtype=mode)
+    try:
+        def score(n):
+            w = jet_synth.from_lists(pre[:n], cand[:n])
+            p = J.jet_prefill_prefix(m, w.prefix_offsets, w.prefix_tokens)
+            tok, _ = J.jet_score_candidates(m, p, w.q_cand_offsets, w.cand_tok_offsets, w.cand_tokens)
+            J.jet_prefix_free(p)
+            return tok
+
+        tok = score(20)
+        for n in (1, 3, 6, 9):
+            np.testing.assert_array_equal(score(n), tok[:35 * n], err_msg=f"{35 * n} rows")
+    finally:
+        J.jet_model_free(m)
+    ref, _ = oracle.score_unshared(path, jet_synth.from_lists(pre[:2], cand[:2]))
+    assert np.max(np.abs(tok[:70] - ref)) <= (1e-4 if mode == J.JET_BF16 else 2e-2)
