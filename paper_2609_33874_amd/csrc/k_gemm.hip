@@ -7,7 +7,7 @@
 // pair mode the hi and lo planes of A share each B tile) fed by direct
 // global->LDS loads, one barrier per K step. Problems of few tiles
 // take the smaller tiles of gemm_small.h; which one is chosen by the estimated
-// time of its rounds of workgroups (small_tile_for). Tiles are ordered so that
+// time of its rounds of workgroups (tile_for). Tiles are ordered so that
 // each XCD works on a contiguous band (see tile_coords).
 #include <algorithm>
 #include <cmath>
@@ -390,19 +390,29 @@ using HalfB = GCfg<f16, 256, 256, 128, 128, 11, 1, 2, 8>;
 // ... and 128x128 tiles on the LOAD 8 schedule (the last round of a large
 // launch, grouped GEMMs, and problems whose K is too short for the others).
 using HalfS = GCfg<f16, 128, 128, 32, 64, 8, 2, 3, 4>;
-// K loops that the tiles of four waves run.
-static bool wide_k(int K) { return K % 64 == 0 && K >= 128; }
 // (hi, lo) fp16 pair A operands: the bf16 pair schedules with fp16 operands
 using HalfPairB = GCfg<f16, 256, 256, 128, 128, 12, 2, 3, 4>;
 using HalfPairS = GCfg<f16, 128, 128, 32, 64, 7, 2, 3, 4>;
 // 256x256 tiles of eight waves of 64 x 128, two per SIMD, for work that one wave
-// per SIMD cannot hide behind another's: the RoPE epilogue, whose loads of
-// positions and angles and 2-byte stores it waits for. QKV of 2048 x 1536, us with eight waves and
+// per SIMD cannot hide behind another's: the first loads and the epilogue of a
+// short K (below), and the RoPE epilogue, whose loads of positions and angles
+// and 2-byte stores it waits for. QKV of 2048 x 1536, us with eight waves and
 // with four: 57600 rows fp16 530 and 657, pairs 805 and 943; 67000 rows 590 and
 // 750, 905 and 1072.
 using HalfE = GCfg<f16, 256, 256, 64, 128, 8, 2, 3, 4>;
 using PairE = GCfg<bf16, 256, 256, 64, 128, 7, 2, 3, 4>;
 using HalfPairE = GCfg<f16, 256, 256, 64, 128, 7, 2, 3, 4>;
+// Residual add with a short K: 256x128 tiles, two workgroups per CU, so that one
+// tile's fp32 read-modify-write epilogue overlaps another's K loop (17204 x 1920
+// x 128: 47.5 us, 62.5 with HalfE; 17920 x 5120 x 192: 201 and 219).
+using HalfM = GCfg<f16, 256, 128, 64, 64, 8, 2, 3, 4>;
+// K loops that the tiles of four waves run, and faster than those of eight.
+// Launches of 128 tiles and more, time with four waves over time with eight:
+// fp16 1.09-1.19 at K = 128, 1.06-1.18 at 256, 0.97-1.10 at 512, 0.99-1.07 at
+// 640, 0.90-1.02 at 768, 0.95-1.02 at 1536; pairs 1.02-1.23, 1.05-1.21,
+// 0.99-1.11, 1.03-1.21, 0.96-1.15 and 0.98-1.01.
+constexpr int kShortK = 768;
+static bool wide_k(int K) { return K % 64 == 0 && K >= kShortK; }
 // LM head: the 256x256 schedules transposed (F rows x 256 vocabulary rows), and
 // 64- and 128-row tiles for few rows.
 template <typename T, bool PAIR>
@@ -512,22 +522,53 @@ static int cheapest_of(int epi, int M, int N, int K, double *us) {
   return cheapest(SmallPlain<T, NPL, QB>::cost, M, N, K, us);
 }
 
-// The small tile to use for a problem, or -1 where the 256x256 tiles (big:
-// their cost per round, in the same model; null: there are none) are the
-// cheaper ones or no small tile runs this K. The 256x256 tiles keep every
-// launch of 1024 or more such tiles: over so many rounds the last one does not
-// matter, and per element they are the fastest.
+// The tile to use for a problem: a small one (its index), kMid (128x128 tiles
+// of eight waves, two workgroups per CU), or kBig (256x256 tiles).
+enum { kBig = -1, kMid = -2 };
+
+// big and mid: costs of the 256x256 tiles (per round of 256) and of the 128x128
+// ones (per round of 512), null where they are not considered. The 256x256
+// tiles keep every launch of 1024 or more of them (where mid is considered, of
+// 512): over so many rounds the last one does not matter, and per
+// element they are the fastest. kBig too where nothing else runs this K.
 template <typename T, int NPL, int QB>
-static int small_tile_for(int epi, int M, int N, int K, const TileCost *big) {
+static int tile_for(int epi, int M, int N, int K, const TileCost *big, const TileCost *mid) {
   const int64_t big_tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
-  if (big_tiles >= 1024) return -1;
+  if (epi == EPI_STORE_T && (NPL == 2 || QB)) return big_tiles >= 512 ? kBig : kMid;  // (no small tiles)
+  if (big_tiles >= (mid ? 512 : 1024)) return kBig;
   double us = big ? tile_us(*big, M, N, K) : INFINITY;
-  return cheapest_of<T, NPL, QB>(epi, M, N, K, &us);
+  int best = kBig;
+  if (mid) {
+    const int64_t tiles = (int64_t)((M + mid->bm - 1) / mid->bm) * ((N + mid->bn - 1) / mid->bn);
+    const double t = (double)((tiles + 511) / 512) * (mid->a + mid->b * K / 1000.0);
+    if (t < us) us = t, best = kMid;
+  }
+  const int c = cheapest_of<T, NPL, QB>(epi, M, N, K, &us);
+  return c >= 0 ? c : best;
 }
 
 // Costs of the 256x256 tiles: fp16, (hi, lo) pairs, block-quantized B.
 static constexpr TileCost kBigF16{256, 256, 32, 1, 14.0, 23.0}, kBigPair{256, 256, 32, 1, 12.0, 43.0},
     kBigQ{256, 256, 32, 1, 14.0, 27.0};
+// K too short for the tiles of four waves: the 256x256 tiles of eight. And the
+// 128x128 ones, considered up to K = 1536: from there on the small tiles are
+// faster (block-quantized B: below 768, or where no small tile runs K). Fitted
+// to 370 launches of each kind of 64 <= K < 1536, 1 to 32768 rows, 384 to 40000
+// columns, three epilogues. Time against 128x128 tiles below 512 256x256 ones
+// and those from there on, in the mean and at worst: fp16 0.82 and 1.13 below K
+// = 768, 0.65 and 1.04 above, pairs 0.79 and 1.11, 0.69 and 1.06 (with the
+// small tiles and those of four waves alone 0.89 and 1.80, 0.65 and 1.18; pairs
+// 0.82 and 1.66, 0.67 and 1.32).
+static constexpr TileCost kShortF16{256, 256, 32, 1, 10.0, 25.0}, kShortPair{256, 256, 32, 1, 6.0, 25.0},
+    kMidF16{128, 128, 32, 1, 4.0, 20.0}, kMidPair{128, 128, 32, 1, 4.0, 14.0}, kMidQ{128, 128, 32, 1, 5.0, 17.0};
+
+template <typename T, int NPL>
+static int float_tile_for(int epi, int M, int N, int K) {
+  const bool wide = wide_k(K), mid = K < 1536;
+  if constexpr (NPL == 2)
+    return tile_for<T, 2, 0>(epi, M, N, K, wide ? &kBigPair : &kShortPair, mid ? &kMidPair : nullptr);
+  else return tile_for<T, 1, 0>(epi, M, N, K, wide ? &kBigF16 : &kShortF16, mid ? &kMidF16 : nullptr);
+}
 
 // Arguments of one GEMM launch.
 template <typename T>
@@ -539,38 +580,50 @@ static GemmArgs<T> gemm_args(const void *A, int64_t lda, const void *B, int64_t 
   return g;
 }
 
+// Pair operands: small tiles, 128x128 (S), 256x256 of four (B) or eight (E) waves.
+template <class B, class E, class S>
+static hipError_t run_pair(int epi, const void *A, int64_t lda, const void *Bm, int64_t ldb, int M, int N, int K,
+                           void *out, int64_t ldo, float oscale, hipStream_t st) {
+  using T = typename B::type;
+  const int c = float_tile_for<T, 2>(epi, M, N, K);
+  if (c >= 0) {
+    const GemmArgs<T> g = gemm_args<T>(A, lda, Bm, ldb, M, N, K, 1, out, ldo, oscale);
+    if constexpr (std::is_same_v<T, f16>) return small_gemm_f16p(epi, c, g, st);
+    else return small_gemm_bf16p(epi, c, g, st);
+  }
+  if (c == kMid) return run_epi<S>(epi, A, lda, Bm, ldb, M, N, K, 1, out, ldo, oscale, st);
+  return wide_k(K) ? run_epi<B>(epi, A, lda, Bm, ldb, M, N, K, 1, out, ldo, oscale, st)
+                   : run_epi<E>(epi, A, lda, Bm, ldb, M, N, K, 1, out, ldo, oscale, st);
+}
+
+template <class C>
+static hipError_t run_epi_tail(int epi, const void *A, int64_t lda, const void *B, int64_t ldb, int M, int N, int K,
+                               void *out, int64_t ldo, float oscale, hipStream_t st) {
+  switch (epi) {
+    case EPI_STORE_F32: return run_gemm_tail<C, 0>(A, lda, B, ldb, M, N, K, out, ldo, oscale, st);
+    case EPI_RESID_ADD: return run_gemm_tail<C, 1>(A, lda, B, ldb, M, N, K, out, ldo, oscale, st);
+    case EPI_SWIGLU: return run_gemm_tail<C, 2>(A, lda, B, ldb, M, N, K, out, ldo, oscale, st);
+    default: return run_gemm_tail<C, 3>(A, lda, B, ldb, M, N, K, out, ldo, oscale, st);
+  }
+}
+
 hipError_t launch_gemm(int dtype, int epi, const void *A, int64_t lda, const void *B, int64_t ldb, int M, int N,
                        int K, int pair, void *out, int64_t ldo, float oscale, hipStream_t st) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  const int64_t big_tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
   if (dtype == 0) {
-    if (pair) {
-      const int c = epi == EPI_STORE_T ? -1 : small_tile_for<bf16, 2, 0>(epi, M, N, K, &kBigPair);
-      if (c >= 0) return small_gemm_bf16p(epi, c, gemm_args<bf16>(A, lda, B, ldb, M, N, K, 1, out, ldo, oscale), st);
-      // (few tiles only where K is too short for the small tiles' ring)
-      return big_tiles >= 128 && wide_k(K) ? run_epi<PairB>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st)
-                              : run_epi<PairS>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st);
-    }
+    if (pair) return run_pair<PairB, PairE, PairS>(epi, A, lda, B, ldb, M, N, K, out, ldo, oscale, st);
+    const int64_t big_tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
     if (big_tiles >= 512) return run_epi<BigB>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st);
     return run_epi<SmallB>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st);
   }
   if (dtype == 2) {
-    if (pair) {
-      const int c = epi == EPI_STORE_T ? -1 : small_tile_for<f16, 2, 0>(epi, M, N, K, &kBigPair);
-      if (c >= 0) return small_gemm_f16p(epi, c, gemm_args<f16>(A, lda, B, ldb, M, N, K, 1, out, ldo, oscale), st);
-      return big_tiles >= 128 && wide_k(K) ? run_epi<HalfPairB>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st)
-                              : run_epi<HalfPairS>(epi, A, lda, B, ldb, M, N, K, pair, out, ldo, oscale, st);
-    }
-    const int c = small_tile_for<f16, 1, 0>(epi, M, N, K, &kBigF16);
+    if (pair) return run_pair<HalfPairB, HalfPairE, HalfPairS>(epi, A, lda, B, ldb, M, N, K, out, ldo, oscale, st);
+    const int c = float_tile_for<f16, 1>(epi, M, N, K);
     if (c >= 0) return small_gemm_f16(epi, c, gemm_args<f16>(A, lda, B, ldb, M, N, K, 0, out, ldo, oscale), st);
-    if (big_tiles < 128 || !wide_k(K))
-      return run_epi<HalfS>(epi, A, lda, B, ldb, M, N, K, 0, out, ldo, oscale, st);
-    switch (epi) {
-      case EPI_STORE_F32: return run_gemm_tail<HalfB, 0>(A, lda, B, ldb, M, N, K, out, ldo, oscale, st);
-      case EPI_RESID_ADD: return run_gemm_tail<HalfB, 1>(A, lda, B, ldb, M, N, K, out, ldo, oscale, st);
-      case EPI_SWIGLU: return run_gemm_tail<HalfB, 2>(A, lda, B, ldb, M, N, K, out, ldo, oscale, st);
-      default: return run_gemm_tail<HalfB, 3>(A, lda, B, ldb, M, N, K, out, ldo, oscale, st);
-    }
+    if (c == kMid) return run_epi<HalfS>(epi, A, lda, B, ldb, M, N, K, 0, out, ldo, oscale, st);
+    if (wide_k(K)) return run_epi_tail<HalfB>(epi, A, lda, B, ldb, M, N, K, out, ldo, oscale, st);
+    if (epi == EPI_RESID_ADD) return run_gemm_tail<HalfM, 1>(A, lda, B, ldb, M, N, K, out, ldo, oscale, st);
+    return run_epi_tail<HalfE>(epi, A, lda, B, ldb, M, N, K, out, ldo, oscale, st);
   }
   return run_epi<CfgF>(epi, A, lda, B, ldb, M, N, K, 0, out, ldo, oscale, st);
 }
@@ -599,28 +652,29 @@ static hipError_t run_q8_epi(int epi, const void *A, int64_t lda, const void *Bq
   }
 }
 
-hipError_t launch_gemm_q8(int epi, const void *A, int64_t lda, const void *Bq, const uint16_t *Bs, int M, int N,
-                          int K, void *out, int64_t ldo, float oscale, hipStream_t st) {
+// Block-quantized B of QB bits: small tiles, 128x128 (S), 256x256 (B).
+template <int QB, class B, class S>
+static hipError_t run_quant(int epi, const void *A, int64_t lda, const void *Bq, const uint16_t *Bs, int M, int N, int K,
+                            void *out, int64_t ldo, float oscale, hipStream_t st) {
   if (M <= 0 || N <= 0) return hipSuccess;
   if (K % 32 != 0) return hipErrorInvalidValue;
-  const int c = epi == EPI_STORE_T ? -1 : small_tile_for<f16, 1, 8>(epi, M, N, K, &kBigQ);
-  if (c >= 0)
-    return small_gemm_q8(epi, c, gemm_args<f16>(A, lda, Bq, (int64_t)K * 8 / 8, M, N, K, 0, out, ldo, oscale, Bs), st);
-  const int64_t big_tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
-  if (big_tiles >= 128) return run_q8_epi<Q8B>(epi, A, lda, Bq, Bs, M, N, K, out, ldo, oscale, st);
-  return run_q8_epi<Q8S>(epi, A, lda, Bq, Bs, M, N, K, out, ldo, oscale, st);
+  const int c = tile_for<f16, 1, QB>(epi, M, N, K, &kBigQ, K < kShortK || K % 128 ? &kMidQ : nullptr);
+  if (c >= 0) {
+    const GemmArgs<f16> g = gemm_args<f16>(A, lda, Bq, (int64_t)K * QB / 8, M, N, K, 0, out, ldo, oscale, Bs);
+    return QB == 8 ? small_gemm_q8(epi, c, g, st) : small_gemm_q4(epi, c, g, st);
+  }
+  return c == kMid ? run_q8_epi<S>(epi, A, lda, Bq, Bs, M, N, K, out, ldo, oscale, st)
+                   : run_q8_epi<B>(epi, A, lda, Bq, Bs, M, N, K, out, ldo, oscale, st);
+}
+
+hipError_t launch_gemm_q8(int epi, const void *A, int64_t lda, const void *Bq, const uint16_t *Bs, int M, int N,
+                          int K, void *out, int64_t ldo, float oscale, hipStream_t st) {
+  return run_quant<8, Q8B, Q8S>(epi, A, lda, Bq, Bs, M, N, K, out, ldo, oscale, st);
 }
 
 hipError_t launch_gemm_q4(int epi, const void *A, int64_t lda, const void *Bq, const uint16_t *Bs, int M, int N,
                           int K, void *out, int64_t ldo, float oscale, hipStream_t st) {
-  if (M <= 0 || N <= 0) return hipSuccess;
-  if (K % 32 != 0) return hipErrorInvalidValue;
-  const int c = epi == EPI_STORE_T ? -1 : small_tile_for<f16, 1, 4>(epi, M, N, K, &kBigQ);
-  if (c >= 0)
-    return small_gemm_q4(epi, c, gemm_args<f16>(A, lda, Bq, (int64_t)K * 4 / 8, M, N, K, 0, out, ldo, oscale, Bs), st);
-  const int64_t big_tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
-  if (big_tiles >= 128) return run_q8_epi<Q4B>(epi, A, lda, Bq, Bs, M, N, K, out, ldo, oscale, st);
-  return run_q8_epi<Q4S>(epi, A, lda, Bq, Bs, M, N, K, out, ldo, oscale, st);
+  return run_quant<4, Q4B, Q4S>(epi, A, lda, Bq, Bs, M, N, K, out, ldo, oscale, st);
 }
 
 template <class C, int EPI>
@@ -666,7 +720,7 @@ static hipError_t run_grouped_epi(int epi, const void *A, int64_t lda, const voi
 int gemm_group_rows(int dtype, double avg, int d, int F) {
   if (dtype == 1) return CfgF::BM;
   if (dtype != 2) return SmallB::BM;
-  if (avg >= 512.0 && wide_k(d) && wide_k(F)) return HalfB::BM;
+  if (avg >= 512.0) return HalfB::BM;
   if (avg >= 64.0) return HalfS::BM;
   using S = SmallSwiglu<f16, 1, 0>;
   using P = SmallPlain<f16, 1, 0>;
@@ -682,6 +736,8 @@ hipError_t launch_gemm_grouped(int dtype, int bm, int epi, const void *A, int64_
                                int64_t ldo, float oscale, hipStream_t st) {
   if (M <= 0 || N <= 0) return hipSuccess;
   if (!tile_group || bm <= 0 || M % bm) return hipErrorInvalidValue;
+  if (dtype == 2 && bm == HalfB::BM && !wide_k(K))
+    return run_grouped_epi<HalfE>(epi, A, lda, B, ldb, group_stride, tile_group, M, N, K, out, ldo, oscale, st);
   if (dtype == 2 && bm == HalfB::BM)
     return run_grouped_epi<HalfB>(epi, A, lda, B, ldb, group_stride, tile_group, M, N, K, out, ldo, oscale, st);
   if (dtype == 2 && bm == HalfS::BM)
@@ -719,11 +775,11 @@ static hipError_t run_qkv_rope(const void *A, int64_t lda, const void *B, int64_
 // projection and the rotation run as two kernels (block-quantized B of K = 128,
 // shorter than the ring of any small tile, or of 1024 256x256 tiles and more).
 static int rope_tile_for(int dtype, int qbits, int pair, int M, int N, int K) {
-  if (qbits == 8) return small_tile_for<f16, 1, 8>(EPI_QKV_ROPE, M, N, K, nullptr);
-  if (qbits == 4) return small_tile_for<f16, 1, 4>(EPI_QKV_ROPE, M, N, K, nullptr);
-  if (dtype == 0) return pair ? small_tile_for<bf16, 2, 0>(EPI_QKV_ROPE, M, N, K, &kBigPair) : -1;
-  if (pair) return small_tile_for<f16, 2, 0>(EPI_QKV_ROPE, M, N, K, &kBigPair);
-  return small_tile_for<f16, 1, 0>(EPI_QKV_ROPE, M, N, K, &kBigF16);
+  if (qbits == 8) return tile_for<f16, 1, 8>(EPI_QKV_ROPE, M, N, K, nullptr, nullptr);
+  if (qbits == 4) return tile_for<f16, 1, 4>(EPI_QKV_ROPE, M, N, K, nullptr, nullptr);
+  if (dtype == 0) return pair ? tile_for<bf16, 2, 0>(EPI_QKV_ROPE, M, N, K, &kBigPair, nullptr) : -1;
+  if (pair) return tile_for<f16, 2, 0>(EPI_QKV_ROPE, M, N, K, &kBigPair, nullptr);
+  return tile_for<f16, 1, 0>(EPI_QKV_ROPE, M, N, K, &kBigF16, nullptr);
 }
 static bool rope_big_ok(int dtype, int qbits, int pair, int M, int N) {
   return !qbits && (dtype == 2 || (dtype == 0 && pair)) &&

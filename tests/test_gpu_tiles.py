@@ -46,6 +46,12 @@ CASES = {
     # oracle is left out: a rounding difference may swap experts of equal logit)
     "experts": (dict(DENSE, dtype="bf16", d_model=512, ffn=512, n_experts=16, top_k=2, moe_ffn=512, shared_ffn=512),
                 J.JET_F16),
+    # ... and a gate/up product on the 256-row tiles of four waves
+    "experts_wide": (dict(DENSE, dtype="bf16", d_model=1024, ffn=512, n_experts=16, top_k=2, moe_ffn=512,
+                          shared_ffn=512), J.JET_F16),
+    # 128x128 and 256x256 tiles of int8 / int4 weights where no small tile runs K
+    "q8_odd_k": (dict(DENSE, dtype="q8", d_model=384, ffn=960), J.JET_F16),
+    "q4_odd_k": (dict(DENSE, dtype="q4", d_model=384, ffn=960), J.JET_F16),
     "experts_hybrid": (dict(DENSE, arch="hybrid", n_layers=4, dtype="bf16", d_model=512, ffn=512, n_experts=16,
                             top_k=2, moe_ffn=512, shared_ffn=512, gdn_heads=2, gdn_dk=128, gdn_dv=128,
                             conv_kernel=4), J.JET_F16),
