@@ -41,10 +41,13 @@ DEFAULT_DTYPE = {"dense_27b_k10": "bf16", "hybrid_4b_k4": "bf16"}
 
 # Sources of each kernel class: a counter summary under profiles/ holds the
 # hash of these files as they were when the counters were taken.
+# (The files of its kernels and what they include, but for the launchers'
+# declarations in kernels.h.)
+_GEMM = ["device.h", "gemm_args.h", "gemm_core.h", "gemm_small.h", "gemm_small_tiles.h", "k_gemm.hip"]
 KERNEL_SOURCES = {
-    "gemm": ["device.h", "gemm_core.h", "k_gemm.hip"],
-    "lmhead": ["device.h", "gemm_core.h", "k_gemm.hip"],
-    "attn": ["device.h", "k_attn.hip"],
+    "gemm": _GEMM + [f"k_gemm_small_{k}.hip" for k in ("bf16p", "f16", "f16p", "q4", "q8")],
+    "lmhead": _GEMM,
+    "attn": ["attn_common.h", "device.h", "gemm_core.h", "k_attn.hip", "k_attn16.hip"],
     "gdn": ["device.h", "k_gdn.hip"],
 }
 
