@@ -6,8 +6,9 @@
 // K loop, one or two workgroups per CU, so nothing but the workgroup's own
 // loads in flight hides the memory latency and nothing but short dependent
 // chains hides the MFMA latency. Hence
-//   * K steps of 128 columns in a ring of NS LDS stages, NS - 1 steps of direct
-//     global->LDS loads in flight, one barrier per step;
+//   * K steps of 128 columns (64 in the largest tiles) in a ring of NS LDS
+//     stages, NS - 1 steps of direct global->LDS loads in flight, one barrier
+//     per step;
 //   * 16x16x32 MFMAs: a quarter of the 32x32x16 product's output per wave, so
 //     four times the waves share a tile and a K step's dependent chain is 4
 //     short MFMAs instead of 8 long ones.
@@ -83,9 +84,6 @@ __device__ __forceinline__ int small_col(int wn, int j) {
   else return (wn * C::NI + j) * 16;
 }
 
-// acc += A[m0 ..][K] * B[n0 ..][K]^T over a workgroup's tile. ldb and the
-// byte layout of a quantized B as in launch_gemm_q8 / _q4. Needs K a multiple
-// of BK and K / BK >= NS - 1. Rows past M / N load the last valid row.
 // RoPE tiles of 32 columns: 16 dims d and the 16 dims d + 64 of one head (four
 // tiles per head), so that few rows still spread over many CUs.
 template <class C, int EPI>
@@ -108,6 +106,9 @@ __device__ __forceinline__ int small_swz(int r) {
   return CH == 16 ? (r & 15) : CH == 8 ? ((r >> 1) & 7) : ((r >> 2) & 3);
 }
 
+// acc = A[m0 ..][K] * B[n0 ..][K]^T over a workgroup's tile. ldb_bytes and the
+// byte layout of a quantized B as in launch_gemm_q8 / _q4. Needs K a multiple
+// of BK and K / BK >= NS - 1. Rows past M / N load the last valid row.
 template <class C, int EPI>
 __device__ __forceinline__ void small_tile(const typename C::type *__restrict__ A, int64_t lda, const char *B,
                                            int64_t ldb_bytes, const uint16_t *__restrict__ Bs, int M, int N, int K,

@@ -13,8 +13,12 @@ enum { SMALL_F16 = 0, SMALL_F16P = 1, SMALL_BF16P = 2, SMALL_Q8 = 3, SMALL_Q4 = 
 // One round of workgroups (one per CU) takes about a + b K / 1000
 // microseconds. Fitted to launches of one to three rounds on one MI355X,
 // weights coming from memory (decoder shapes N = 1536 .. 19456, K = 1536 ..
-// 9728, 8 to 6000 rows); launches of up to 256 workgroups reproduce within
-// 15%, which is what the choice between tiles needs.
+// 9728, 8 to 6000 rows). In a kernel trace, launches of up to 256 workgroups take
+// the estimated time within 15% on the plain tiles, and 1.15 to 1.5 times it on
+// the SwiGLU and RoPE ones (K = 1536: SwiGLU 16 x 128 13.7 us for 9.3, 64 x 128
+// 16.7 for 12.0, 256 x 128 28.0 for 24; RoPE 32 x 32 7.2 for 5.4, 64 x 32 8.5 for
+// 6.7): too little alike in all of them, which the choice between the tiles of
+// one epilogue needs, but not the line to the 256x256 ones.
 struct TileCost {
   int bm, bn, bk, ahead;
   double a, b;

@@ -4,8 +4,8 @@
 // 25% slower than two of this kernel: 3.20 against 2.57 ms, 27B prefix of
 // 16,868 rows).
 //
-// One workgroup (4 waves) takes up to 64 query slots of one (question, KV
-// head): slot s is query head kvh * G + s % G at row s / G, so the G query
+// One workgroup (4 waves) takes up to 64 query slots (16-bit planes: or 128,
+// attn_block) of one (question, KV head): slot s is query head kvh * G + s % G at row s / G, so the G query
 // heads that share a KV head share every K/V tile the workgroup stages in
 // LDS, a block's rows lie within 64 / G of each other (causal prefix blocks
 // stop at nearly the same key), and consecutive lanes read consecutive heads
@@ -431,7 +431,14 @@ constexpr int attn_qb() {
 // 128 slots: each staged tile and each K / V fragment read from LDS serves
 // twice the queries of 64. 64 where the registers hold no more (pairs, fp32),
 // where most of a 128-slot item would be idle, and where the 128-slot items
-// would leave half of the CUs without one.
+// would leave half of the CUs without one, so that a launch is one chain of
+// key tiles, which is shorter for 64. Prefixes, 12 query and 2 KV heads, us with
+// 128 and with 64 slots: one of 1300 rows (122 items of 128) head_dim 128 44 and
+// 34, 64 49 and 32, 32 43 and 28; 8 of 160 rows (128 items) 13.2 and 11.7, 11.9
+// and 10.1, 10.7 and 8.9. Candidates of a question of 1300 rows: 52 and 35, 58
+// and 35, 51 and 31. Above the line 64 slots are still ahead for few or long
+// prefixes (one of 1800 rows, 170 items, 56 and 42, 65 and 41, 58 and 36; 4 of
+// 1400, 528 items, 58 and 56, 59 and 45, 51 and 45).
 int attn_block(int dtype, int pair, int mode, double slots, double total) {
   if (dtype == 1 || pair || (mode == 1 && slots < 96.0)) return 64;
   return total < 128.0 * 128.0 ? 64 : 128;

@@ -59,7 +59,8 @@ def gpu_trace_and_scores(path, wl, dtype, n, tau, seed, steps=None):
 def model_path(spec, model_dir):
     if spec == "wide_ffn_bf16":
         # the small dense model with a 2048-wide FFN: the decode steps' down
-        # projection (K = 2048, 4 rows) then takes the split-K GEMM path
+        # projection (K = 2048, 4 rows) then runs on the 32x16 GEMM tiles, whose
+        # ring of six stages of 128 columns turns over (K = 768 just fills it)
         import os
         p = os.path.join(model_dir, "wide_ffn_bf16.jetm")
         if not os.path.exists(p):
