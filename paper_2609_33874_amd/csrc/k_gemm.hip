@@ -714,7 +714,8 @@ static hipError_t run_grouped_epi(int epi, const void *A, int64_t lda, const voi
 // gate/up, F for down), for segments of `avg` rows on average. A tile belongs
 // to one expert, so the padding is half a tile per expert. 256-row tiles
 // (fp16) from 512 rows a segment: at 656 rows (256 experts, d 2048, F 512)
-// gate/up took 1190 us with 128-row tiles and takes 1010, down 755 and 691.
+// gate/up took 1190 us with 128-row tiles and 1010 with 256-row ones of eight
+// waves, down 755 and 691 (gate/up on those of four waves, at 656 rows: 839).
 // 128-row tiles from 64; below, small tiles, where the stream of the experts'
 // weights bounds the launch, as far as K fills their ring of stages (46 rows:
 // gate/up 346 -> 279 us with 64-row tiles, down 197 -> 208; 16-row tiles up to
